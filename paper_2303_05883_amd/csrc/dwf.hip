@@ -18,9 +18,8 @@
 // same links (one cache line serves them all) and spinors at consecutive j, and
 // the s-hops come from the neighbouring lanes through LDS. A launch covers
 // both parities. The workgroups walk the lattice in an XCD-aware order
-// (dwf_site, dwf_walk): each XCD takes a range of x columns, y rows or z
-// planes in every slice and walks it so that the neighbours of the sites in
-// flight were read shortly before by the same XCD and may still be in its L2.
+// (dwf_site, dwf_walk): each XCD takes a compact region and walks it in bricks
+// of about the sites it has in flight, both parities of a brick at once.
 //
 // Kernels per application: D with c5 = 0 (b5 folded into the diagonal and the
 // hop scale) and D^dag are one kernel each; D with c5 != 0 first forms
@@ -41,6 +40,21 @@ namespace {
 
 constexpr int DWB = 256;  // largest workgroup; a workgroup holds whole 4-d sites (a multiple of Ls lanes)
 
+// Division of a 31-bit unsigned number by a fixed one: a high multiply and two
+// shifts (the round-up method with the 33rd bit of the multiplier implicit).
+struct Div {
+  unsigned m, s, d;
+};
+Div make_div(unsigned d) {
+  unsigned l = 0;
+  while (l < 31 && (1u << l) < d) ++l;
+  return {(unsigned)((((unsigned long long)1 << 32) * (((unsigned long long)1 << l) - d)) / d + 1), l ? l - 1 : 0, d};
+}
+__device__ inline unsigned quot(unsigned n, const Div& v) {
+  const unsigned t = __umulhi(n, v.m);
+  return v.d == 1 ? n : (t + ((n - t) >> 1)) >> v.s;
+}
+
 struct DwfArgs {
   const char* gauge;
   size_t link_stride;
@@ -50,10 +64,12 @@ struct DwfArgs {
   char* out;
   size_t hb;  // bytes of one parity half
   int Ls;
-  int spb;   // 5-d sites per workgroup
-  int walk;  // 0: linear order; 1: XCD z-slabs of hw planes (lz = 8 hw); 2: XCD y-ranges of hw rows (ly = 8 hw);
-             // 3: XCD x-ranges of hw checkerboard columns (lx/2 = 8 hw)
-  int hw;
+  Div dLs;
+  int ns4;    // 4-d sites per workgroup
+  unsigned nreg;     // 4-d sites of one parity in one XCD's region
+  int sp[3], rg[4];  // regions per direction (x, y, z; the rest in t) and their extents (x in checkerboard columns)
+  int bk[4];         // brick extents
+  Div dvol, dbk[3], dnb[3];  // brick volume, brick extents, bricks per region and direction
   double d4;         // 4 - M5
   double b5, c5, mf;
   double* norm;      // k_dwf: partial sums of |out|^2, a (0, value) pair per workgroup, or null
@@ -61,81 +77,141 @@ struct DwfArgs {
   double upd_beta;
 };
 
-// The 5-d site of this lane, or false past the end. XCD k (the workgroups
-// are dealt to the 8 XCDs round-robin) takes
-//   walk 1: the slab z in [k hw, (k+1) hw), walked x, y fastest, then z, then
-//           t: the z and t neighbours were read one z plane or one slab slice
-//           earlier;
-//   walk 2: the rows y in [k hw, (k+1) hw), walked x fastest, then those rows,
-//           then t, then z: the t neighbours were read one step earlier and the
-//           z neighbours lt steps earlier, a working set of lt + 1 slices of
-//           lx/2 x hw sites (the neighbours of the two edge rows come from the
-//           other XCDs' ranges);
-//   walk 3: the checkerboard columns xh in [k hw, (k+1) hw), walked those
-//           columns fastest, then t, then z, then y: the t and z neighbours were
-//           read hw and hw lt sites earlier and the y neighbours one y step
-//           (hw lt lz sites) earlier, so the span between the first and the last
-//           read of a spinor is two y steps (2 hw lt lz sites, about 5.5 MB of
-//           FP64 traffic through the XCD's L2 at 64x32x16x8 x 8, against 11 MB
-//           for the z neighbours of walk 2); only the x neighbours of the two
-//           edge columns come from other XCDs (a quarter of a spinor per site
-//           at hw = 4, against half of one for the y edges of walk 2).
-// All Ls lanes of a 4-d site are in one workgroup in every walk.
-__device__ inline bool dwf_site(const DwfArgs& a, size_t& j) {
-  const Geom& g = a.g;
-  if (threadIdx.x >= a.spb) return false;
-  if (a.walk == 0) {
-    j = (size_t)blockIdx.x * a.spb + threadIdx.x;
-    return j < (size_t)g.vh * a.Ls;
+// The walk. The lattice is cut into 8 equal regions, one per XCD (workgroups
+// reach the XCDs round-robin: blk mod 8), and every XCD walks its region brick
+// by brick, so that the sites in flight on it form a compact 4-d brick of both
+// parities whose neighbours are mostly each other: a spinor is read from
+// memory about once by each brick that touches it, as own site of one parity
+// and as neighbour of the other. The site of slot q of workgroup blk:
+// coordinates c = (x column, y, z, t); false past the region's end.
+__device__ inline bool dwf_site(const DwfArgs& a, unsigned blk, unsigned slot, int c[4]) {
+  const unsigned q = (blk >> 3) * (unsigned)a.ns4 + slot;
+  unsigned ib = quot(q, a.dvol), w = q - ib * a.dvol.d, k = blk & 7;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    unsigned wl = w, bl = ib, kl = k;
+    if (d < 3) {
+      const unsigned wq = quot(w, a.dbk[d]), bq = quot(ib, a.dnb[d]), kq = k / (unsigned)a.sp[d];
+      wl = w - wq * a.dbk[d].d;
+      bl = ib - bq * a.dnb[d].d;
+      kl = k - kq * a.sp[d];
+      w = wq;
+      ib = bq;
+      k = kq;
+    }
+    c[d] = (int)(kl * a.rg[d] + bl * a.bk[d] + wl);
   }
-  const int k = blockIdx.x & 7;
-  const size_t q = (size_t)(blockIdx.x >> 3) * a.spb + threadIdx.x;
-  const size_t q4 = q / a.Ls, s = q - q4 * a.Ls;
-  if (a.walk == 1) {
-    const size_t xy = (size_t)g.lxh * g.ly;
-    if (q4 >= xy * a.hw * g.lt) return false;
-    const size_t xyi = q4 % xy, rest = q4 / xy;
-    const size_t zin = rest % a.hw, t = rest / a.hw;
-    j = (xyi + xy * ((size_t)k * a.hw + zin + (size_t)g.lz * t)) * a.Ls + s;
-    return true;
-  }
-  if (a.walk == 3) {
-    if (q4 >= (size_t)a.hw * g.lt * g.lz * g.ly) return false;
-    const size_t xin = q4 % a.hw;
-    size_t rest = q4 / a.hw;
-    const size_t t = rest % g.lt;
-    rest /= g.lt;
-    const size_t z = rest % g.lz, y = rest / g.lz;
-    j = ((size_t)k * a.hw + xin + (size_t)g.lxh * (y + (size_t)g.ly * (z + (size_t)g.lz * t))) * a.Ls + s;
-    return true;
-  }
-  const size_t rows = (size_t)g.lxh * a.hw;
-  if (q4 >= rows * g.lt * g.lz) return false;
-  const size_t xr = q4 % rows, rest = q4 / rows;
-  const size_t t = rest % g.lt, z = rest / g.lt;
-  const size_t xin = xr % g.lxh, yin = xr / g.lxh;
-  j = (xin + (size_t)g.lxh * ((size_t)k * a.hw + yin + (size_t)g.ly * (z + (size_t)g.lz * t))) * a.Ls + s;
-  return true;
+  return q < a.nreg;
 }
 
-// The walk of a lattice: LQCD_DWF_WALK (0 linear, 1 z-slabs, 2 y-ranges,
-// 3 x-ranges) where it fits the lattice, else x-ranges for FP64 fields where
-// lx/2 is a multiple of 8, else y-ranges where ly is, else z-slabs where lz
-// is, else linear; returns the grid's workgroup count for n 5-d sites of one
-// parity. The x-ranges cut the FP64 spinor re-reads (each XCD keeps whole
-// rows of its columns' neighbours); in FP32 a cache line of a link component
-// spans 32 checkerboard sites of a row, so columns of lx/16 sites would fetch
-// every link line on several XCDs, and the y-ranges are kept.
-unsigned dwf_walk(const Geom& g, DwfArgs& a, size_t n, int prec) {
-  const bool x_ok = g.lxh % 8 == 0, y_ok = g.ly % 8 == 0, z_ok = g.lz % 8 == 0;
-  int w = (prec == 0 && x_ok) ? 3 : (y_ok ? 2 : (z_ok ? 1 : 0));
+__device__ inline int dwf_index(const Geom& g, const int c[4]) {
+  return c[0] + g.lxh * (c[1] + g.ly * (c[2] + g.lz * c[3]));
+}
+
+// This lane's 5-d site: coordinates, s, checkerboard index i and 5-d index j
+struct Site5 {
+  int c[4], s, i;
+  size_t j;
+  bool live;
+};
+
+__device__ inline Site5 dwf_lane(const DwfArgs& a, unsigned blk) {
+  Site5 l;
+  const unsigned slot = quot(threadIdx.x, a.dLs);
+  l.s = (int)(threadIdx.x - slot * a.Ls);
+  l.live = dwf_site(a, blk, slot, l.c) && (int)slot < a.ns4;
+  if (!l.live) l.c[0] = l.c[1] = l.c[2] = l.c[3] = l.s = 0;
+  l.i = dwf_index(a.g, l.c);
+  l.j = (size_t)l.i * a.Ls + l.s;
+  return l;
+}
+
+// A launch over both parities: 8 workgroups (one per XCD) of the even sites,
+// then the 8 of the same slots of the odd sites, so that both parities of a
+// brick are in flight on one XCD at the same time.
+__device__ inline unsigned dwf_both(int& p) {
+  p = (blockIdx.x >> 3) & 1;
+  return (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);
+}
+
+// Chooses regions and bricks and returns the workgroups of one parity. Regions:
+// the split of the four directions into 8 whose regions have the least surface
+// per site, rows of at least 8 columns first (a 128-byte line holds one 16-byte
+// word of 8 sites); the split 1 x 2 x 2 x 2 always fits, ly, lz and lt being
+// even. Bricks: the
+// region cut down to at most 8192 / Ls sites of one parity, about what one XCD
+// has in flight (64x32x16x8 x 8, D^dag in FP64: bricks of
+// 256 to 1024 sites took 328-347 us, slabs of single columns or planes 344-390;
+// 32^4 x 8: 1267-1326 us against 1334-1843). LQCD_DWF_WALK forces another order
+// (0 regions in t, y and z, 1 regions in z, 2 in y, 3 in x where they fit, each
+// walked without bricks); results do not depend on it.
+unsigned dwf_walk(const Geom& g, DwfArgs& a) {
+  const int L[4] = {g.lxh, g.ly, g.lz, g.lt};
+  const double wt[4] = {0.5, 1.0, 1.0, 0.9};  // an x column is two sites; a t hop reads half a spinor
+  auto cost = [&](const int e[4]) {
+    double c = 0.0;
+    for (int d = 0; d < 4; ++d)
+      if (e[d] < L[d]) c += wt[d] / e[d];
+    return c + (e[0] < 8 && e[0] < L[0] ? 10.0 : 0.0);
+  };
+  int force = -1;
   if (const char* env = std::getenv("LQCD_DWF_WALK")) {
     const int f = std::atoi(env);
-    if (f == 0 || (f == 1 && z_ok) || (f == 2 && y_ok) || (f == 3 && x_ok)) w = f;
+    if (f == 0 || (f == 1 && L[2] % 8 == 0) || (f == 2 && L[1] % 8 == 0) || (f == 3 && L[0] % 8 == 0)) force = f;
   }
-  a.walk = w;
-  a.hw = w == 3 ? g.lxh / 8 : (w == 2 ? g.ly / 8 : (w == 1 ? g.lz / 8 : 0));
-  return w ? 8u * (unsigned)((n / 8 + a.spb - 1) / a.spb) : (unsigned)((n + a.spb - 1) / a.spb);
+  int sp[4] = {1, 2, 2, 2};
+  if (force > 0) {
+    sp[1] = sp[2] = sp[3] = 1;
+    sp[3 - force] = 8;
+  } else if (force < 0) {
+    double best = 1e30;
+    for (int sx = 1; sx <= 8; sx *= 2)
+      for (int sy = 1; sx * sy <= 8; sy *= 2)
+        for (int sz = 1; sx * sy * sz <= 8; sz *= 2) {
+          const int q[4] = {sx, sy, sz, 8 / (sx * sy * sz)};
+          if (L[0] % q[0] || L[1] % q[1] || L[2] % q[2] || L[3] % q[3]) continue;
+          const int e[4] = {L[0] / q[0], L[1] / q[1], L[2] / q[2], L[3] / q[3]};
+          const double c = cost(e);
+          if (c < best) {
+            best = c;
+            for (int d = 0; d < 4; ++d) sp[d] = q[d];
+          }
+        }
+  }
+  a.nreg = 1;
+  for (int d = 0; d < 4; ++d) {
+    a.bk[d] = a.rg[d] = L[d] / sp[d];
+    a.nreg *= (unsigned)a.rg[d];
+    if (d < 3) a.sp[d] = sp[d];
+  }
+  // bricks: from the whole region, the cut by a smallest prime factor that adds
+  // the least surface, until the brick holds at most 8192 / Ls sites
+  while (force < 0 && (long)a.bk[0] * a.bk[1] * a.bk[2] * a.bk[3] > std::max(64, 8192 / a.Ls)) {
+    double best = 1e30;
+    int dir = 0, ext = 1;
+    for (int d = 0; d < 4; ++d) {
+      int f = 2;
+      while (f * f <= a.bk[d] && a.bk[d] % f) ++f;
+      if (a.bk[d] % f) f = a.bk[d];
+      if (a.bk[d] == 1) continue;
+      int e[4] = {a.bk[0], a.bk[1], a.bk[2], a.bk[3]};
+      e[d] /= f;
+      if (const double c = cost(e); c < best) {
+        best = c;
+        dir = d;
+        ext = e[d];
+      }
+    }
+    a.bk[dir] = ext;
+  }
+  a.ns4 = DWB / a.Ls;
+  a.dLs = make_div(a.Ls);
+  a.dvol = make_div((unsigned)(a.bk[0] * a.bk[1] * a.bk[2] * a.bk[3]));
+  for (int d = 0; d < 3; ++d) {
+    a.dbk[d] = make_div(a.bk[d]);
+    a.dnb[d] = make_div(a.rg[d] / a.bk[d]);
+  }
+  return 8u * ((a.nreg + a.ns4 - 1) / a.ns4);
 }
 
 // The s-neighbours of a lane: P_+ and P_- of every lane's field x go to LDS
@@ -186,44 +262,45 @@ __device__ inline void add_s(const SNeighbours<T>& n, T f, cx<T> o[12]) {
   }
 }
 
+// The 8 hops of a 4-d site of parity p in the order +x, -x, +y, -y, ...: the
+// neighbour's checkerboard index, and where its link lies (the forward links at
+// the site itself, the backward ones at the neighbour).
+__device__ inline void dwf_neighbours(const Geom& g, int p, const int c[4], int i, int nb[8]) {
+  const int y = c[1], z = c[2], t = c[3];
+  const int x = 2 * c[0] + ((y + z + t + p) & 1), row = i - c[0];
+  const int yl = g.lxh, zl = g.lxh * g.ly, tl = g.lxh * g.ly * g.lz;
+  nb[0] = row + (((x + 1 == g.lx) ? 0 : x + 1) >> 1);
+  nb[1] = row + (((x == 0) ? g.lx - 1 : x - 1) >> 1);
+  nb[2] = i + ((y + 1 == g.ly) ? -(g.ly - 1) * yl : yl);
+  nb[3] = i + ((y == 0) ? (g.ly - 1) * yl : -yl);
+  nb[4] = i + ((z + 1 == g.lz) ? -(g.lz - 1) * zl : zl);
+  nb[5] = i + ((z == 0) ? (g.lz - 1) * zl : -zl);
+  nb[6] = i + ((t + 1 == g.lt) ? -(g.lt - 1) * tl : tl);
+  nb[7] = i + ((t == 0) ? (g.lt - 1) * tl : -tl);
+}
+
 // H (DAG: gamma5 H gamma5) of the other parity of f5 at this lane's 5-d site
 template <int P, bool DAG>
-__device__ inline void dwf_hop(const DwfArgs& a, const char* f5, int p, int i, int s, cx<typename IO<P>::T> acc[12]) {
+__device__ inline void dwf_hop(const DwfArgs& a, const char* f5, int p, const Site5& l,
+                               cx<typename IO<P>::T> acc[12]) {
   const Geom& g = a.g;
-  const int Ls = a.Ls;
   const char* other = f5 + (size_t)(1 - p) * a.hb;
-  const int xh = i % g.lxh;
-  int r = i / g.lxh;
-  const int y = r % g.ly;
-  r /= g.ly;
-  const int z = r % g.lz;
-  const int t = r / g.lz;
-  const int x = 2 * xh + ((y + z + t + p) & 1);
-  const int row = i - xh;
-  const int xf = (x + 1 == g.lx) ? 0 : x + 1;
-  const int xb = (x == 0) ? g.lx - 1 : x - 1;
-  const int yl = g.lxh, zl = g.lxh * g.ly, tl = g.lxh * g.ly * g.lz;
-  const int ixf = row + (xf >> 1), ixb = row + (xb >> 1);
-  const int iyf = i + ((y + 1 == g.ly) ? -(g.ly - 1) * yl : yl);
-  const int iyb = i + ((y == 0) ? (g.ly - 1) * yl : -yl);
-  const int izf = i + ((z + 1 == g.lz) ? -(g.lz - 1) * zl : zl);
-  const int izb = i + ((z == 0) ? (g.lz - 1) * zl : -zl);
-  const int itf = i + ((t + 1 == g.lt) ? -(g.lt - 1) * tl : tl);
-  const int itb = i + ((t == 0) ? (g.lt - 1) * tl : -tl);
-  const bool flipf = (g.t_bc < 0) && (t + 1 == g.lt);
-  const bool flipb = (g.t_bc < 0) && (t == 0);
+  int nb[8];
+  dwf_neighbours(g, p, l.c, l.i, nb);
+  const bool flipf = (g.t_bc < 0) && (l.c[3] + 1 == g.lt);
+  const bool flipb = (g.t_bc < 0) && (l.c[3] == 0);
   const char* gf = a.gauge + (size_t)(p * 4) * a.link_stride;
   const char* gb = a.gauge + (size_t)((1 - p) * 4) * a.link_stride;
   const size_t ls = a.link_stride, vh = (size_t)g.vh;
-  auto at = [&](int site) { return (size_t)site * Ls + s; };
-  hop_dir<P, 0, true, false, DAG>(other, gf + 0 * ls, vh, at(ixf), (size_t)i, false, acc);
-  hop_dir<P, 0, false, false, DAG>(other, gb + 0 * ls, vh, at(ixb), (size_t)ixb, false, acc);
-  hop_dir<P, 1, true, false, DAG>(other, gf + 1 * ls, vh, at(iyf), (size_t)i, false, acc);
-  hop_dir<P, 1, false, false, DAG>(other, gb + 1 * ls, vh, at(iyb), (size_t)iyb, false, acc);
-  hop_dir<P, 2, true, false, DAG>(other, gf + 2 * ls, vh, at(izf), (size_t)i, false, acc);
-  hop_dir<P, 2, false, false, DAG>(other, gb + 2 * ls, vh, at(izb), (size_t)izb, false, acc);
-  hop_dir<P, 3, true, false, DAG>(other, gf + 3 * ls, vh, at(itf), (size_t)i, flipf, acc);
-  hop_dir<P, 3, false, false, DAG>(other, gb + 3 * ls, vh, at(itb), (size_t)itb, flipb, acc);
+  auto at = [&](int site) { return (size_t)site * a.Ls + l.s; };
+  hop_dir<P, 0, true, false, DAG>(other, gf + 0 * ls, vh, at(nb[0]), (size_t)l.i, false, acc);
+  hop_dir<P, 0, false, false, DAG>(other, gb + 0 * ls, vh, at(nb[1]), (size_t)nb[1], false, acc);
+  hop_dir<P, 1, true, false, DAG>(other, gf + 1 * ls, vh, at(nb[2]), (size_t)l.i, false, acc);
+  hop_dir<P, 1, false, false, DAG>(other, gb + 1 * ls, vh, at(nb[3]), (size_t)nb[3], false, acc);
+  hop_dir<P, 2, true, false, DAG>(other, gf + 2 * ls, vh, at(nb[4]), (size_t)l.i, false, acc);
+  hop_dir<P, 2, false, false, DAG>(other, gb + 2 * ls, vh, at(nb[5]), (size_t)nb[5], false, acc);
+  hop_dir<P, 3, true, false, DAG>(other, gf + 3 * ls, vh, at(nb[6]), (size_t)l.i, flipf, acc);
+  hop_dir<P, 3, false, false, DAG>(other, gb + 3 * ls, vh, at(nb[7]), (size_t)nb[7], flipb, acc);
   if (DAG) {  // gamma5 on the hop of gamma5 psi
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -233,6 +310,17 @@ __device__ inline void dwf_hop(const DwfArgs& a, const char* f5, int p, int i, i
     }
   }
 }
+
+// The hop kernels are bound by the spinors that miss an XCD's L2: the sites in
+// flight (2 waves per SIMD at 188 VGPRs in FP64, 4 in FP32) hold 3 MB of spinors
+// per XCD of the 4 MB it has, so what is not a neighbour of what is in flight is
+// read again. Hence the bricks, both parities interleaved, and the result
+// stored past the cache (nothing reads it again in this launch). Measured for
+// D^dag, 64x32x16x8 x 8, against single columns or rows of one parity at a time:
+// FP64 370 -> 318 us, FP32 180 -> 156 us; 32^4 x 8: FP64 2.14 -> 1.26 ms, FP32
+// 711 -> 619 us; 16^4 x 8: FP64 154 -> 81 us. Links staged through LDS for the
+// Ls lanes of a site measured equal (326 and 157 us), three waves per SIMD
+// slower (spills).
 
 // D (DAG false) or D^dag (DAG true) at every 5-d site. MOB (D only, c5 != 0):
 // the hop acts on phi = (b5 + c5 S) psi, precomputed.
@@ -244,17 +332,17 @@ template <int P, bool DAG, bool MOB>
 __global__ void __launch_bounds__(DWB) k_dwf(DwfArgs a) {
   using T = typename IO<P>::T;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
-  const int p = blockIdx.y, Ls = a.Ls;
-  size_t j = 0;
-  const bool live = dwf_site(a, j);
-  const int i = live ? (int)(j / Ls) : 0;
-  const int s = live ? (int)(j - (size_t)i * Ls) : 0;
+  int p;
+  const Site5 l = dwf_lane(a, dwf_both(p));
+  const int Ls = a.Ls, s = l.s;
+  const size_t j = l.j;
+  const bool live = l.live;
   const char* own = a.in + (size_t)p * a.hb;
 
   cx<T> acc[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) acc[k] = {T(0), T(0)};
-  if (live) dwf_hop<P, DAG>(a, MOB ? a.phi : a.in, p, i, s, acc);
+  if (live) dwf_hop<P, DAG>(a, MOB ? a.phi : a.in, p, l, acc);
   cx<T> v[12];
   if (live) {
     IO<P>::load_spinor(own, j, v);
@@ -298,13 +386,13 @@ __global__ void __launch_bounds__(DWB) k_dwf(DwfArgs a) {
       for (int k = 0; k < 12; ++k) o[k] = dg * v[k] + sc * acc[k];
       add_s<false>(nb, T(-1), o);
     }
-    IO<P>::store_spinor(a.out + (size_t)p * a.hb, j, o);
+    IO<P>::template store_spinor<true>(a.out + (size_t)p * a.hb, j, o);
   }
   if (a.norm) {  // uniform over the launch: the workgroup's partial |out|^2, slot 1 of its pair
     double nv[2] = {0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < 12; ++k) nv[1] += (double)o[k].r * (double)o[k].r + (double)o[k].i * (double)o[k].i;
-    block_reduce<2>(nv, a.norm + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 2);
+    block_reduce<2>(nv, a.norm + (size_t)blockIdx.x * 2);
   }
 }
 
@@ -315,10 +403,11 @@ template <int P>
 __global__ void __launch_bounds__(DWB) k_dwf_phi(DwfArgs a) {
   using T = typename IO<P>::T;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
-  const int p = blockIdx.y;
-  size_t j = 0;
-  const bool live = dwf_site(a, j);
-  const int s = live ? (int)(j % (size_t)a.Ls) : 0;
+  int p;
+  const Site5 l = dwf_lane(a, dwf_both(p));
+  const int s = l.s;
+  const size_t j = l.j;
+  const bool live = l.live;
   cx<T> v[12];
   if (live) {
     IO<P>::load_spinor(a.in + (size_t)p * a.hb, j, v);
@@ -361,10 +450,10 @@ __global__ void __launch_bounds__(DWB) k_dwf_sop(DwfArgs a, int p, const char* x
                                                  const double* mats, const char* r5, double beta) {
   using T = typename IO<P>::T;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
-  const int Ls = a.Ls;
-  size_t j = 0;
-  const bool live = dwf_site(a, j);
-  const int s = live ? (int)(j % (size_t)Ls) : 0;
+  const Site5 l = dwf_lane(a, blockIdx.x);
+  const int Ls = a.Ls, s = l.s;
+  const size_t j = l.j;
+  const bool live = l.live;
   const int base = (int)threadIdx.x - s;
   cx<T> o[12];
 #pragma unroll
@@ -421,17 +510,16 @@ __global__ void __launch_bounds__(DWB) k_dwf_hopsop(DwfArgs a, int p, double sca
                                                     const double* mx, const double* my, double* norm_partials) {
   using T = typename IO<P>::T;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
-  const int Ls = a.Ls;
-  size_t j = 0;
-  const bool live = dwf_site(a, j);
-  const int i = live ? (int)(j / Ls) : 0;
-  const int s = live ? (int)(j - (size_t)i * Ls) : 0;
+  const Site5 l = dwf_lane(a, blockIdx.x);
+  const int Ls = a.Ls, s = l.s;
+  const size_t j = l.j;
+  const bool live = l.live;
   const int base = (int)threadIdx.x - s;
   cx<T> y[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) y[k] = {T(0), T(0)};
   if (live) {
-    dwf_hop<P, DAG>(a, a.in, p, i, s, y);
+    dwf_hop<P, DAG>(a, a.in, p, l, y);
     const T sc = (T)scale;
 #pragma unroll
     for (int k = 0; k < 12; ++k) y[k] = sc * y[k];
@@ -470,7 +558,7 @@ __global__ void __launch_bounds__(DWB) k_dwf_hopsop(DwfArgs a, int p, double sca
       }
     }
   }
-  if (live) IO<P>::store_spinor(a.out + (size_t)p * a.hb, j, o);
+  if (live) IO<P>::template store_spinor<true>(a.out + (size_t)p * a.hb, j, o);
   if (norm_partials) {  // uniform over the launch
     double v[2] = {0.0, 0.0};
     if (live) {
@@ -639,10 +727,10 @@ int dwf_export(lqcd_ctx* c, int prec, int Ls, const void* f5, double* canon) {
 }
 
 // workgroups of one dwf_apply launch (both parities): the pairs its norm_partials receive
-size_t dwf_apply_groups(const Geom& g, int prec, int Ls) {
+size_t dwf_apply_groups(const Geom& g, int Ls) {
   DwfArgs a{};
-  a.spb = (DWB / Ls) * Ls;
-  return 2 * (size_t)dwf_walk(g, a, (size_t)g.vh * Ls, prec);
+  a.Ls = Ls;
+  return 2 * (size_t)dwf_walk(g, a);
 }
 
 // out = D in (dag = 0) or D^dag in (dag = 1) on native 5-d fields (in != out;
@@ -664,13 +752,12 @@ int dwf_apply(lqcd_ctx* c, int prec, const lqcd_dwf_params& d, int dag, const vo
   a.out = reinterpret_cast<char*>(out);
   a.hb = half_bytes(prec, c->g.vh, d.Ls);
   a.Ls = d.Ls;
-  a.spb = (DWB / d.Ls) * d.Ls;
   a.d4 = 4.0 - d.M5;
   a.b5 = d.b5;
   a.c5 = d.c5;
   a.mf = d.mf;
-  const unsigned nb = dwf_walk(c->g, a, (size_t)c->g.vh * d.Ls, prec);
-  const dim3 grid(nb, 2), block((a.spb + 63) / 64 * 64);
+  const unsigned nb = dwf_walk(c->g, a);
+  const dim3 grid(2 * nb), block((a.ns4 * d.Ls + 63) / 64 * 64);
   a.norm = norm_partials;
   if (mob) {
     DwfArgs f = a;
@@ -784,7 +871,7 @@ int dwf_solve(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params& pr
   void *bn, *r, *p, *q, *t, *ph;
   for (void** f : {&bn, &r, &p, &q, &t, &ph}) LQ_TRY(w.alloc(c, bytes, f));
   // pairs for the flat reductions (one per 256 sites) and for the norm of D p (one per operator workgroup)
-  const size_t ngroups = dwf_apply_groups(c->g, 0, d.Ls);
+  const size_t ngroups = dwf_apply_groups(c->g, d.Ls);
   LQ_HIP(hipMalloc(&w.partials, std::max((size_t)(n + 255) / 256, ngroups) * 2 * sizeof(double)));
   double bb = 0.0;
   LQ_TRY(dot(c, w, n, b, b, nullptr, &bb));
@@ -1022,13 +1109,12 @@ int eo_setup(lqcd_ctx* c, int prec, const lqcd_dwf_params& d, const double* mats
   a.g = c->g;
   a.hb = half_bytes(prec, c->g.vh, d.Ls);
   a.Ls = d.Ls;
-  a.spb = (DWB / d.Ls) * d.Ls;
   a.d4 = 4.0 - d.M5;
   a.b5 = d.b5;
   a.c5 = d.c5;
   a.mf = d.mf;
-  e.grid = dim3(dwf_walk(c->g, a, (size_t)c->g.vh * d.Ls, prec));
-  e.block = dim3((a.spb + 63) / 64 * 64);
+  e.grid = dim3(dwf_walk(c->g, a));
+  e.block = dim3((a.ns4 * d.Ls + 63) / 64 * 64);
   return LQCD_OK;
 }
 

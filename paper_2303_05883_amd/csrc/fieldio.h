@@ -12,7 +12,7 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 typedef float fvec4 __attribute__((ext_vector_type(4)));
 
-// 16- and 8-byte loads; NT = non-temporal (streamed once, kept out of the caches'
+// 16-byte loads and stores and 8-byte loads; NT = non-temporal (streamed once, kept out of the caches'
 // reuse set so that neighbour spinors stay resident).
 template <bool NT>
 __device__ inline double2 ld16(const double2* p) {
@@ -29,6 +29,16 @@ __device__ inline float4 ld16(const float4* p) {
     return make_float4(v.x, v.y, v.z, v.w);
   }
   return *p;
+}
+template <bool NT>
+__device__ inline void st16(double2* p, double2 v) {
+  if (NT) __builtin_nontemporal_store(dvec2{v.x, v.y}, reinterpret_cast<dvec2*>(p));
+  else *p = v;
+}
+template <bool NT>
+__device__ inline void st16(float4* p, float4 v) {
+  if (NT) __builtin_nontemporal_store(fvec4{v.x, v.y, v.z, v.w}, reinterpret_cast<fvec4*>(p));
+  else *p = v;
 }
 template <bool NT>
 __device__ inline half4 ld8(const half4* p) {
@@ -92,10 +102,11 @@ struct IO<0> {
     load_half(f, i, upper, s);
     scale = T(1);
   }
+  template <bool NT = false>
   __device__ static inline void store_spinor(void* f, size_t i, const cx<T> s[12]) {
     double2* b = reinterpret_cast<double2*>(f);
 #pragma unroll
-    for (int k = 0; k < 12; ++k) b[widx(i, k, 12)] = make_double2(s[k].r, s[k].i);
+    for (int k = 0; k < 12; ++k) st16<NT>(b + widx(i, k, 12), make_double2(s[k].r, s[k].i));
   }
   // words k with k % nl == lane (the lanes of one site share the stores)
   __device__ static inline void store_part(void* f, size_t i, const cx<T> s[12], int lane, int nl) {
@@ -167,11 +178,12 @@ struct IO<1> {
     load_half(f, i, upper, s);
     scale = T(1);
   }
+  template <bool NT = false>
   __device__ static inline void store_spinor(void* f, size_t i, const cx<T> s[12]) {
     float4* b = reinterpret_cast<float4*>(f);
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-      b[widx(i, k, 6)] = make_float4(s[2 * k].r, s[2 * k].i, s[2 * k + 1].r, s[2 * k + 1].i);
+      st16<NT>(b + widx(i, k, 6), make_float4(s[2 * k].r, s[2 * k].i, s[2 * k + 1].r, s[2 * k + 1].i));
   }
   __device__ static inline void store_part(void* f, size_t i, const cx<T> s[12], int lane, int nl) {
     float4* b = reinterpret_cast<float4*>(f);
