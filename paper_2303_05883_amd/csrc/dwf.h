@@ -5,6 +5,8 @@
 
 namespace lq {
 
+struct CgState;  // cg.h
+
 // Bytes of a native 5-d field: two parity halves, each site-blocked over the
 // 5-d index i Ls + s (i the 4-d checkerboard index), even half first.
 size_t dwf_field_bytes(int prec, size_t vh, int Ls);
@@ -15,9 +17,10 @@ int dwf_export(lqcd_ctx* c, int prec, int Ls, const void* f5, double* canon);
 // third 5-d field, needed (phi) by D with c5 != 0 only; norm_partials: if
 // given, the launch's workgroups write their partial sums of |out|^2 as
 // (0, value) pairs, dwf_apply_groups of them; upd (D with c5 != 0 only): in
-// is first replaced in place by upd + upd_beta in (a CG direction update)
+// is first replaced in place by upd + beta in (a CG direction update, beta from
+// cg); cg: nothing is done when that solve is done
 int dwf_apply(lqcd_ctx* c, int prec, const lqcd_dwf_params& d, int dag, const void* in, void* out, void* tmp,
-              double* norm_partials = nullptr, const void* upd = nullptr, double upd_beta = 0.0);
+              double* norm_partials = nullptr, const void* upd = nullptr, const CgState* cg = nullptr);
 size_t dwf_apply_groups(const Geom& g, int Ls);
 // Even-odd form (4-d parity): out_e = S_ee in_e (dag 0) or S_ee^dag in_e (dag
 // 1), S_ee = M5op - Dhop_eo M5op^-1 Dhop_oe; only the even halves of in and

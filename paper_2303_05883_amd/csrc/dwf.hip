@@ -31,6 +31,7 @@
 #include <cstdlib>
 #include <vector>
 
+#include "cg.h"
 #include "dwf.h"
 #include "hopcore.h"
 #include "internal.h"
@@ -73,8 +74,8 @@ struct DwfArgs {
   double d4;         // 4 - M5
   double b5, c5, mf;
   double* norm;      // k_dwf: partial sums of |out|^2, a (0, value) pair per workgroup, or null
-  const char* upd;   // k_dwf_phi: in is first replaced in place by upd + upd_beta in (or null)
-  double upd_beta;
+  const char* upd;   // k_dwf_phi: in is first replaced in place by upd + beta in, cg's beta (or null)
+  const CgState* cg;  // if set: nothing is done when this solve is done
 };
 
 // The walk. The lattice is cut into 8 equal regions, one per XCD (workgroups
@@ -331,6 +332,7 @@ __device__ inline void dwf_hop(const DwfArgs& a, const char* f5, int p, const Si
 template <int P, bool DAG, bool MOB>
 __global__ void __launch_bounds__(DWB) k_dwf(DwfArgs a) {
   using T = typename IO<P>::T;
+  if (a.cg && a.cg->done) return;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
   int p;
   const Site5 l = dwf_lane(a, dwf_both(p));
@@ -397,11 +399,12 @@ __global__ void __launch_bounds__(DWB) k_dwf(DwfArgs a) {
 }
 
 // out = (b5 + c5 S) in, every 5-d site; with a.upd, in is first replaced at
-// this lane's site by upd + upd_beta in and stored back (a CG search-direction
+// this lane's site by upd + beta in and stored back (a CG search-direction
 // update fused into the operator, whose later kernel reads in at its own site)
 template <int P>
 __global__ void __launch_bounds__(DWB) k_dwf_phi(DwfArgs a) {
   using T = typename IO<P>::T;
+  if (a.cg && a.cg->done) return;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
   int p;
   const Site5 l = dwf_lane(a, dwf_both(p));
@@ -414,7 +417,7 @@ __global__ void __launch_bounds__(DWB) k_dwf_phi(DwfArgs a) {
     if (a.upd) {
       cx<T> rv[12];
       IO<P>::load_spinor(a.upd + (size_t)p * a.hb, j, rv);
-      const T bt = (T)a.upd_beta;
+      const T bt = (T)a.cg->beta;
 #pragma unroll
       for (int k = 0; k < 12; ++k) v[k] = rv[k] + bt * v[k];
       IO<P>::store_spinor(const_cast<char*>(a.in) + (size_t)p * a.hb, j, v);
@@ -443,12 +446,13 @@ __global__ void __launch_bounds__(DWB) k_dwf_phi(DwfArgs a) {
 
 // out_s = sum_s' (A_+ P_+ x + A_- P_- x)_s' [+ (C_+ P_+ y + C_- P_- y)_s'] on the
 // parity-p half of 5-d fields; mats = {A_+, A_-, C_+, C_-}, each Ls x Ls row-major.
-// With r5 (x part only), x is first replaced by r + beta x at this lane's site
-// and stored back (a CG search-direction update fused into the operator).
+// With r5 (x part only), x is first replaced by r + beta x (beta of a.cg) at
+// this lane's site and stored back (a CG search-direction update fused into the operator).
 template <int P>
 __global__ void __launch_bounds__(DWB) k_dwf_sop(DwfArgs a, int p, const char* x5, const char* y5,
-                                                 const double* mats, const char* r5, double beta) {
+                                                 const double* mats, const char* r5) {
   using T = typename IO<P>::T;
+  if (a.cg && a.cg->done) return;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
   const Site5 l = dwf_lane(a, blockIdx.x);
   const int Ls = a.Ls, s = l.s;
@@ -469,7 +473,7 @@ __global__ void __launch_bounds__(DWB) k_dwf_sop(DwfArgs a, int p, const char* x
       if (pass == 0 && r5) {
         cx<T> rv[12];
         IO<P>::load_spinor(r5 + (size_t)p * a.hb, j, rv);
-        const T bt = (T)beta;
+        const T bt = (T)a.cg->beta;
 #pragma unroll
         for (int k = 0; k < 12; ++k) v[k] = rv[k] + bt * v[k];
         IO<P>::store_spinor(const_cast<char*>(f) + (size_t)p * a.hb, j, v);
@@ -509,6 +513,7 @@ template <int P, bool DAG>
 __global__ void __launch_bounds__(DWB) k_dwf_hopsop(DwfArgs a, int p, double scale, const char* x5,
                                                     const double* mx, const double* my, double* norm_partials) {
   using T = typename IO<P>::T;
+  if (a.cg && a.cg->done) return;
   __shared__ cx<T> lp[6][DWB], lm[6][DWB];
   const Site5 l = dwf_lane(a, blockIdx.x);
   const int Ls = a.Ls, s = l.s;
@@ -629,9 +634,11 @@ __global__ void __launch_bounds__(256) k_flat_axpy(void* out, const void* a, con
 // The CG update in one pass: x += alpha p, r -= alpha q, and the
 // per-workgroup partial sums of |r|^2 in FP64 (slot 1 of each pair, as k_flat_dot)
 template <int P>
-__global__ void __launch_bounds__(256) k_flat_xr(void* x, const void* p, void* r, const void* q, double alpha,
+__global__ void __launch_bounds__(256) k_flat_xr(void* x, const void* p, void* r, const void* q, const CgState* st,
                                                  double* partials, size_t n) {
   using T = typename IO<P>::T;
+  if (st->done) return;
+  const double alpha = st->alpha;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[2] = {0.0, 0.0};
   if (i < n) {
@@ -652,6 +659,22 @@ __global__ void __launch_bounds__(256) k_flat_xr(void* x, const void* p, void* r
     IO<P>::store_spinor(r, i, a);
   }
   block_reduce<2>(v, partials + (size_t)blockIdx.x * 2);
+}
+
+// CG direction: p = r + beta p
+template <int P>
+__global__ void __launch_bounds__(256) k_flat_dir(void* p, const void* r, const CgState* st, size_t n) {
+  using T = typename IO<P>::T;
+  if (st->done) return;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const T beta = (T)st->beta;
+  cx<T> a[12], b[12];
+  IO<P>::load_spinor(r, i, a);
+  IO<P>::load_spinor(p, i, b);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) a[k] = a[k] + beta * b[k];
+  IO<P>::store_spinor(p, i, a);
 }
 
 // per-workgroup partial sums of Re <a, b> and <b, b> (FP64 sums)
@@ -736,13 +759,13 @@ size_t dwf_apply_groups(const Geom& g, int Ls) {
 // out = D in (dag = 0) or D^dag in (dag = 1) on native 5-d fields (in != out;
 // tmp, a third field, holds phi for D with c5 != 0)
 int dwf_apply(lqcd_ctx* c, int prec, const lqcd_dwf_params& d, int dag, const void* in, void* out, void* tmp,
-              double* norm_partials, const void* upd, double upd_beta) {
+              double* norm_partials, const void* upd, const CgState* cg) {
   if (!c->gauge[prec]) return set_error(LQCD_ESTATE, "gauge field not set");
   if (d.Ls < 1 || d.Ls > DWB) return set_error(LQCD_EINVAL, "domain-wall operator: Ls must be in [1, 256]");
   if (prec != 0 && prec != 1) return set_error(LQCD_EINVAL, "domain-wall operator: precision must be F64 or F32");
   const bool mob = !dag && d.c5 != 0.0;
   if (mob && !tmp) return set_error(LQCD_EINVAL, "domain-wall operator: D with c5 != 0 needs a scratch field");
-  if (upd && !mob) return set_error(LQCD_EINVAL, "domain-wall operator: a fused update needs D with c5 != 0");
+  if (upd && (!mob || !cg)) return set_error(LQCD_EINVAL, "domain-wall operator: a fused update needs D with c5 != 0");
   DwfArgs a{};
   a.gauge = reinterpret_cast<const char*>(c->gauge[prec]);
   a.link_stride = link_bytes(prec, c->g.vh);
@@ -759,12 +782,12 @@ int dwf_apply(lqcd_ctx* c, int prec, const lqcd_dwf_params& d, int dag, const vo
   const unsigned nb = dwf_walk(c->g, a);
   const dim3 grid(2 * nb), block((a.ns4 * d.Ls + 63) / 64 * 64);
   a.norm = norm_partials;
+  a.cg = cg;
   if (mob) {
     DwfArgs f = a;
     f.out = reinterpret_cast<char*>(tmp);
     f.norm = nullptr;
     f.upd = reinterpret_cast<const char*>(upd);
-    f.upd_beta = upd_beta;
     if (prec == 0) hipLaunchKernelGGL(k_dwf_phi<0>, grid, block, 0, c->stream, f);
     else hipLaunchKernelGGL(k_dwf_phi<1>, grid, block, 0, c->stream, f);
   }
@@ -786,7 +809,6 @@ namespace {
 struct DWork {
   std::vector<void*> mem;
   double* partials = nullptr;
-  std::vector<double> host;
   ~DWork() {
     for (void* p : mem) (void)hipFree(p);
     if (partials) (void)hipFree(partials);
@@ -812,24 +834,34 @@ int axpy(lqcd_ctx* c, size_t n, void* out, const void* a, const void* b, double 
   return LQCD_OK;
 }
 
-int sum_partials_host(lqcd_ctx* c, DWork& w, size_t n, double* ab, double* bb);
-
 int dot(lqcd_ctx* c, DWork& w, size_t n, const void* a, const void* b, double* ab, double* bb, int prec = 0) {
   const int nb = (int)((n + 255) / 256);
   if (prec == 0) hipLaunchKernelGGL(k_flat_dot<0>, dim3(nb), dim3(256), 0, c->stream, a, b, w.partials, n);
   else hipLaunchKernelGGL(k_flat_dot<1>, dim3(nb), dim3(256), 0, c->stream, a, b, w.partials, n);
   LQ_HIP(hipGetLastError());
-  return sum_partials_host(c, w, n, ab, bb);
+  return cg_sum_host(c, w.partials, nb, ab, bb);
 }
 
-// x += alpha p, r -= alpha q, *rr = |r|^2 (after the update)
-int xr_update(lqcd_ctx* c, DWork& w, size_t n, void* x, const void* p, void* r, const void* q, double alpha,
-              double* rr, int prec = 0) {
+// CG on n sites of fields of precision prec from x and r until |r| <= target or
+// max_iters iterations. normal() enqueues p = r + beta p (beta from the state: 0
+// before the first iteration, p = r) and q = A p with the partial sums of
+// <p, q> (component 1) in the ngroups pairs of w.partials.
+template <typename F>
+int cg_solve(lqcd_ctx* c, DWork& w, size_t n, size_t ngroups, void* x, void* p, void* r, void* q, double target,
+             int max_iters, int prec, F&& normal, int* iters) {
   const int nb = (int)((n + 255) / 256);
-  if (prec == 0) hipLaunchKernelGGL(k_flat_xr<0>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, alpha, w.partials, n);
-  else hipLaunchKernelGGL(k_flat_xr<1>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, alpha, w.partials, n);
-  LQ_HIP(hipGetLastError());
-  return sum_partials_host(c, w, n, nullptr, rr);
+  CgState* st = cg_state(c);
+  LQ_TRY(axpy(c, n, p, r, r, 0.0, prec));
+  if (prec == 0) hipLaunchKernelGGL(k_flat_dot<0>, dim3(nb), dim3(256), 0, c->stream, r, r, w.partials, n);
+  else hipLaunchKernelGGL(k_flat_dot<1>, dim3(nb), dim3(256), 0, c->stream, r, r, w.partials, n);
+  LQ_TRY(cg_init(c, w.partials, nb, target, max_iters));
+  return cg_run(c, [&]() -> int {
+    LQ_TRY(normal());
+    LQ_TRY(cg_alpha(c, w.partials, ngroups, 1));
+    if (prec == 0) hipLaunchKernelGGL(k_flat_xr<0>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, st, w.partials, n);
+    else hipLaunchKernelGGL(k_flat_xr<1>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, st, w.partials, n);
+    return cg_beta(c, w.partials, nb);
+  }, iters);
 }
 
 int flat_down(lqcd_ctx* c, size_t n, const void* in64, void* out32) {
@@ -841,22 +873,6 @@ int flat_down(lqcd_ctx* c, size_t n, const void* in64, void* out32) {
 int flat_accum_up(lqcd_ctx* c, size_t n, void* x64, const void* e32) {
   hipLaunchKernelGGL(k_flat_accum_up, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, x64, e32, n);
   LQ_HIP(hipGetLastError());
-  return LQCD_OK;
-}
-
-// the sums of the (Re <a, b>, <b, b>) partials of the last reduction, on the host
-int sum_partials_host(lqcd_ctx* c, DWork& w, size_t n, double* ab, double* bb) {
-  const int nb = (int)((n + 255) / 256);
-  w.host.resize((size_t)nb * 2);
-  LQ_HIP(hipMemcpyAsync(w.host.data(), w.partials, w.host.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  LQ_HIP(hipStreamSynchronize(c->stream));
-  double s0 = 0.0, s1 = 0.0;
-  for (size_t k = 0; k < w.host.size(); k += 2) {
-    s0 += w.host[k];
-    s1 += w.host[k + 1];
-  }
-  if (ab) *ab = s0;
-  if (bb) *bb = s1;
   return LQCD_OK;
 }
 
@@ -908,33 +924,20 @@ int dwf_solve(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params& pr
     ++passes;
     LQ_TRY(dwf_apply(c, 0, d, 1, t, r, ph));  // r = D^dag (b - D x)
     LQ_TRY(dot(c, w, n, r, r, nullptr, &rr));
-    LQ_TRY(axpy(c, n, p, r, r, 0.0));             // p = r
     const double tgt = std::min(target, 0.5 * std::sqrt(rr));
     // Moebius D forms phi = (b5 + c5 S) p first, at each site from p there:
     // that pass also does the direction update p = r + beta p
     const bool fuse = d.c5 != 0.0;
-    double beta = 0.0;
-    bool first = true;
-    while (iters < prm.max_iter) {
-      // t = D p, with the partials of |D p|^2
-      LQ_TRY(dwf_apply(c, 0, d, 0, p, t, ph, w.partials, fuse && !first ? r : nullptr, beta));
-      LQ_TRY(dwf_apply(c, 0, d, 1, t, q, ph));              // q = D^dag D p
-      double pq = 0.0;                                       // <p, D^dag D p> = |D p|^2
-      LQ_TRY(sum_partials_host(c, w, ngroups * 256, nullptr, &pq));
-      if (!(pq > 0.0)) break;
-      const double alpha = rr / pq;
-      double rn = 0.0;
-      LQ_TRY(xr_update(c, w, n, x, p, r, q, alpha, &rn));
-      ++iters;
-      if (std::sqrt(rn) <= tgt) {
-        rr = rn;
-        break;
+    const CgState* cs = cg_state(c);
+    LQ_TRY(cg_solve(c, w, n, ngroups, x, p, r, q, tgt, prm.max_iter - iters, 0, [&]() -> int {
+      if (!fuse) {
+        hipLaunchKernelGGL(k_flat_dir<0>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, p, r, cs, n);
+        LQ_HIP(hipGetLastError());
       }
-      beta = rn / rr;
-      first = false;
-      if (!fuse) LQ_TRY(axpy(c, n, p, r, p, beta));
-      rr = rn;
-    }
+      // t = D p, with the partials of |D p|^2 = <p, D^dag D p>; q = D^dag D p
+      LQ_TRY(dwf_apply(c, 0, d, 0, p, t, ph, w.partials, fuse ? r : nullptr, cs));
+      return dwf_apply(c, 0, d, 1, t, q, ph, nullptr, nullptr, cs);
+    }, &iters));
     // the next pass iterates on the recomputed residual to a tighter normal target if needed
     target *= 0.5;
   }
@@ -1044,23 +1047,26 @@ struct EoCtx {
   const double* mats;
   const double* pair(int e) const { return mats + (size_t)e * 2 * d.Ls * d.Ls; }
 
-  // r (optional): x is first replaced in place by r + beta x (x then written)
-  int sop(int p, const void* x, const void* y, int e, void* out, const void* r = nullptr, double beta = 0.0) const {
+  // r (optional, with cg): x is first replaced in place by r + beta x (x then written)
+  int sop(int p, const void* x, const void* y, int e, void* out, const void* r = nullptr,
+          const CgState* cg = nullptr) const {
     DwfArgs b = a;
+    b.cg = cg;
     b.out = reinterpret_cast<char*>(out);
     const char* xs = reinterpret_cast<const char*>(x);
     const char* ys = reinterpret_cast<const char*>(y);
     const char* rs = reinterpret_cast<const char*>(r);
-    if (prec == 0) hipLaunchKernelGGL(k_dwf_sop<0>, grid, block, 0, c->stream, b, p, xs, ys, pair(e), rs, beta);
-    else hipLaunchKernelGGL(k_dwf_sop<1>, grid, block, 0, c->stream, b, p, xs, ys, pair(e), rs, beta);
+    if (prec == 0) hipLaunchKernelGGL(k_dwf_sop<0>, grid, block, 0, c->stream, b, p, xs, ys, pair(e), rs);
+    else hipLaunchKernelGGL(k_dwf_sop<1>, grid, block, 0, c->stream, b, p, xs, ys, pair(e), rs);
     LQ_HIP(hipGetLastError());
     return LQCD_OK;
   }
   // out = scale H in, then the site-local operators of k_dwf_hopsop (x part
   // with pair ex when x is given, y part with pair ey)
   int hopsop(int p, const void* in, const void* x, int ex, int ey, void* out, bool dag,
-             double* norm_partials = nullptr) const {
+             double* norm_partials = nullptr, const CgState* cg = nullptr) const {
     DwfArgs b = a;
+    b.cg = cg;
     b.in = reinterpret_cast<const char*>(in);
     b.out = reinterpret_cast<char*>(out);
     const char* xs = reinterpret_cast<const char*>(x);
@@ -1080,17 +1086,17 @@ struct EoCtx {
   // Each hop is fused with the site-local operator after it (k_dwf_hopsop).
   // norm_partials (dag 0 only): the workgroups' partial sums of |out_e|^2, as
   // (0, value) pairs, one pair per workgroup of grid.
-  // xr (dag 0 only): x_e is first replaced in place by xr_e + beta x_e, the CG
-  // search-direction update, in the first launch.
+  // xr (dag 0 only, with cg): x_e is first replaced in place by xr_e + beta x_e,
+  // the CG search-direction update, in the first launch. cg: as in DwfArgs.
   int schur(int dag, const void* x, void* out, void* tA, void* tB, double* norm_partials = nullptr,
-            const void* xr = nullptr, double beta = 0.0) const {
+            const void* xr = nullptr, const CgState* cg = nullptr) const {
     if (!dag) {
-      LQ_TRY(sop(0, x, nullptr, EP_B, tA, xr, beta));                        // B x
-      LQ_TRY(hopsop(1, tA, nullptr, 0, EP_BMINV, tB, false));                // B M5^-1 Dhop_oe x
-      return hopsop(0, tB, x, EP_M5, EP_MINUS_I, out, false, norm_partials);  // M5 x - Dhop_eo (that)
+      LQ_TRY(sop(0, x, nullptr, EP_B, tA, xr, cg));                                // B x
+      LQ_TRY(hopsop(1, tA, nullptr, 0, EP_BMINV, tB, false, nullptr, cg));         // B M5^-1 Dhop_oe x
+      return hopsop(0, tB, x, EP_M5, EP_MINUS_I, out, false, norm_partials, cg);    // M5 x - Dhop_eo (that)
     }
-    LQ_TRY(hopsop(1, x, nullptr, 0, EP_BMINV_T, tA, true));       // M5^-dag B^dag (-1/2 H^dag_oe x)
-    return hopsop(0, tA, x, EP_M5_T, EP_MINUS_B_T, out, true);   // M5^dag x - B^dag (-1/2 H^dag_eo that)
+    LQ_TRY(hopsop(1, x, nullptr, 0, EP_BMINV_T, tA, true, nullptr, cg));       // M5^-dag B^dag (-1/2 H^dag_oe x)
+    return hopsop(0, tA, x, EP_M5_T, EP_MINUS_B_T, out, true, nullptr, cg);   // M5^dag x - B^dag (-1/2 H^dag_eo that)
   }
 };
 
@@ -1191,19 +1197,14 @@ int dwf_solve_eo(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params&
   LQ_TRY(dot(c, w, nh, ev(sx), ev(sx), nullptr, &sbb));
   int iters = 0, passes = 0, status = LQCD_OK;
   double true_rel = 1.0, target = 0.1 * prm.tol * std::sqrt(sbb);
-  // out_e = S^dag S in_e and *sn = |S in_e|^2 (= <in_e, out_e>, summed by the
-  // workgroups of the operator's last launch: no separate dot product pass)
-  // With rp, in is first updated in place to rp + beta in (the CG direction
-  // update, fused into the operator's first launch).
-  auto normal = [&](void* in, void* out, double* sn, const void* rp, double beta) -> int {
-    LQ_TRY(e.schur(0, in, sx, tA, tB, w.partials, rp, beta));
-    LQ_TRY(e.schur(1, sx, out, tA, tB));
-    return sum_partials_host(c, w, (size_t)e.grid.x * 256, nullptr, sn);
-  };
-  auto normal32 = [&](void* in, void* out, double* sn, const void* rp, double beta) -> int {  // the same in FP32
-    LQ_TRY(e32.schur(0, in, sx32, tA32, tB32, w.partials, rp, beta));
-    LQ_TRY(e32.schur(1, sx32, out, tA32, tB32));
-    return sum_partials_host(c, w, (size_t)e32.grid.x * 256, nullptr, sn);
+  // CG on S^dag S, <p, S^dag S p> taken as |S p|^2 from the workgroups of
+  // S's last launch, the direction update in its first
+  auto cg = [&](const EoCtx& o, void* xv, void* rv, void* p, void* qv, void* s, void* a1, void* a2, double tgt) -> int {
+    const CgState* cs = cg_state(c);
+    return cg_solve(c, w, nh, o.grid.x, xv, p, rv, qv, tgt, prm.max_iter - iters, o.prec, [&]() -> int {
+      LQ_TRY(o.schur(0, p, s, a1, a2, w.partials, rv, cs));
+      return o.schur(1, s, qv, a1, a2, nullptr, nullptr, cs);
+    }, &iters);
   };
   for (;;) {
     // x_o from x_e, then the true residual with the full operator
@@ -1240,46 +1241,14 @@ int dwf_solve_eo(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params&
       // true residual
       LQ_TRY(flat_down(c, nh, ev(r), ev(r32)));
       LQ_HIP(hipMemsetAsync(e32f, 0, half_bytes(1, c->g.vh, d.Ls), c->stream));
-      LQ_TRY(axpy(c, nh, ev(p32), ev(r32), ev(r32), 0.0, 1));
       double rr32 = 0.0;
       LQ_TRY(dot(c, w, nh, ev(r32), ev(r32), nullptr, &rr32, 1));
-      const double tgt32 = std::max(delta * std::sqrt(rr32), target);
-      double beta = 0.0;
-      bool first = true;
-      while (iters < prm.max_iter) {
-        double pq = 0.0;
-        LQ_TRY(normal32(p32, q32, &pq, first ? nullptr : r32, beta));  // p = r + beta p first, after the first
-        if (!(pq > 0.0)) break;
-        const double alpha = rr32 / pq;
-        double rn = 0.0;
-        LQ_TRY(xr_update(c, w, nh, ev(e32f), ev(p32), ev(r32), ev(q32), alpha, &rn, 1));
-        ++iters;
-        if (std::sqrt(rn) <= tgt32) break;
-        beta = rn / rr32;
-        first = false;
-        rr32 = rn;
-      }
+      LQ_TRY(cg(e32, ev(e32f), ev(r32), ev(p32), ev(q32), sx32, tA32, tB32, std::max(delta * std::sqrt(rr32), target)));
       LQ_TRY(flat_accum_up(c, nh, ev(x), ev(e32f)));
       target *= 0.5;
       continue;
     }
-    LQ_TRY(axpy(c, nh, ev(pv), ev(r), ev(r), 0.0));
-    const double tgt = std::min(target, 0.5 * std::sqrt(rr));
-    double beta = 0.0;
-    bool first = true;
-    while (iters < prm.max_iter) {
-      double pq = 0.0;
-      LQ_TRY(normal(pv, q, &pq, first ? nullptr : r, beta));  // p = r + beta p first, after the first
-      if (!(pq > 0.0)) break;
-      const double alpha = rr / pq;
-      double rn = 0.0;
-      LQ_TRY(xr_update(c, w, nh, ev(x), ev(pv), ev(r), ev(q), alpha, &rn));
-      ++iters;
-      if (std::sqrt(rn) <= tgt) break;
-      beta = rn / rr;
-      first = false;
-      rr = rn;
-    }
+    LQ_TRY(cg(e, ev(x), ev(r), ev(pv), ev(q), sx, tA, tB, std::min(target, 0.5 * std::sqrt(rr))));
     target *= 0.5;
   }
   st.outer_iters = passes;

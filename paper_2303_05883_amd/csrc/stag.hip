@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "cg.h"
 #include "fieldio.h"
 #include "internal.h"
 #include "stag.h"
@@ -72,6 +73,7 @@ struct StagArgs {
   void* out;
   double c_own, c_hop;  // out = c_own own + c_hop H in
   double* dot_partials;  // if set (with own): per-workgroup pairs (Re <own, out>, 0)
+  const CgState* cg;     // if set: nothing is done when this solve is done
 };
 
 // out = c_own own + c_hop (H in) at site i of parity p; with dot_partials,
@@ -150,6 +152,7 @@ __device__ inline void stag_hop_site(const StagArgs& a, size_t i, double red[2])
 
 template <int P>
 __global__ void __launch_bounds__(SBS) k_stag_hop(StagArgs a) {
+  if (a.cg && a.cg->done) return;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double red[2] = {0.0, 0.0};
   if (i < (size_t)a.g.vh) stag_hop_site<P>(a, i, red);
@@ -238,9 +241,11 @@ __global__ void __launch_bounds__(SBS) k_stag_dot(const void* a, const void* b, 
 // CG update in one pass: x += alpha p, r -= alpha q, per-workgroup pairs
 // (0, |r|^2) of the updated r (FP64 sums)
 template <int P>
-__global__ void __launch_bounds__(SBS) k_stag_xr(void* x, const void* p, void* r, const void* q, double alpha,
+__global__ void __launch_bounds__(SBS) k_stag_xr(void* x, const void* p, void* r, const void* q, const CgState* st,
                                                  double* partials, size_t vh) {
   using T = typename SIO<P>::T;
+  if (st->done) return;
+  const double alpha = st->alpha;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[2] = {0.0, 0.0};
   if (i < vh) {
@@ -261,6 +266,22 @@ __global__ void __launch_bounds__(SBS) k_stag_xr(void* x, const void* p, void* r
     SIO<P>::store(r, i, a);
   }
   block_reduce<2>(v, partials + (size_t)blockIdx.x * 2);
+}
+
+// CG direction: p = r + beta p
+template <int P>
+__global__ void __launch_bounds__(SBS) k_stag_p(void* p, const void* r, const CgState* st, size_t vh) {
+  using T = typename SIO<P>::T;
+  if (st->done) return;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= vh) return;
+  const T beta = (T)st->beta;
+  cx<T> a[3], b[3];
+  SIO<P>::load(r, i, a);
+  SIO<P>::load(p, i, b);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) a[k] = a[k] + beta * b[k];
+  SIO<P>::store(p, i, a);
 }
 
 // FP64 field rounded to FP32, and x (FP64) += e (FP32)
@@ -310,7 +331,7 @@ int stag_export(lqcd_ctx* c, int prec, int parity, const void* half, double* can
 }
 
 int stag_hop(lqcd_ctx* c, int prec, int out_parity, const void* in, const void* own, double c_own, double c_hop,
-             void* out, double* dot_partials) {
+             void* out, double* dot_partials, const CgState* cg) {
   if (dot_partials && !own) return set_error(LQCD_EINVAL, "staggered hop: a dot product with no own field");
   StagArgs a;
   a.g = c->g;
@@ -323,6 +344,7 @@ int stag_hop(lqcd_ctx* c, int prec, int out_parity, const void* in, const void* 
   a.c_own = c_own;
   a.c_hop = c_hop;
   a.dot_partials = dot_partials;
+  a.cg = cg;
   const int nb = grid_for_sites(c->g.vh);
   if (prec == 0) hipLaunchKernelGGL(k_stag_hop<0>, dim3(nb), dim3(SBS), 0, c->stream, a);
   else hipLaunchKernelGGL(k_stag_hop<1>, dim3(nb), dim3(SBS), 0, c->stream, a);
@@ -335,7 +357,6 @@ namespace {
 struct SWork {
   std::vector<void*> mem;
   double* partials = nullptr;
-  std::vector<double> host;
   ~SWork() {
     for (void* p : mem) (void)hipFree(p);
     if (partials) (void)hipFree(partials);
@@ -360,23 +381,6 @@ int axpby(lqcd_ctx* c, void* out, const void* a, double ca, const void* b = null
   return LQCD_OK;
 }
 
-// the sums of the pairs of the last reduction (one pair per workgroup of a
-// site-parallel launch), on the host in a fixed order
-int sum_pairs(lqcd_ctx* c, SWork& w, double* ab, double* bb) {
-  const int nb = grid_for_sites(c->g.vh);
-  w.host.resize((size_t)nb * 2);
-  LQ_HIP(hipMemcpyAsync(w.host.data(), w.partials, w.host.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  LQ_HIP(hipStreamSynchronize(c->stream));
-  double s0 = 0.0, s1 = 0.0;
-  for (size_t k = 0; k < w.host.size(); k += 2) {
-    s0 += w.host[k];
-    s1 += w.host[k + 1];
-  }
-  if (ab) *ab = s0;
-  if (bb) *bb = s1;
-  return LQCD_OK;
-}
-
 // Re <a, b> and <b, b>
 int dot(lqcd_ctx* c, SWork& w, const void* a, const void* b, double* ab, double* bb, int prec = 0) {
   const int nb = grid_for_sites(c->g.vh);
@@ -384,18 +388,37 @@ int dot(lqcd_ctx* c, SWork& w, const void* a, const void* b, double* ab, double*
   if (prec == 0) hipLaunchKernelGGL(k_stag_dot<0>, dim3(nb), dim3(SBS), 0, c->stream, a, b, w.partials, vh);
   else hipLaunchKernelGGL(k_stag_dot<1>, dim3(nb), dim3(SBS), 0, c->stream, a, b, w.partials, vh);
   LQ_HIP(hipGetLastError());
-  return sum_pairs(c, w, ab, bb);
+  return cg_sum_host(c, w.partials, nb, ab, bb);
 }
 
-// x += alpha p, r -= alpha q, *rr = |r|^2 after the update
-int xr_update(lqcd_ctx* c, SWork& w, void* x, const void* p, void* r, const void* q, double alpha, double* rr,
-              int prec = 0) {
+// One CG iteration on q = (m^2 - H_eo H_oe) p in precision prec: the operator
+// with Re <p, q>, alpha, x += alpha p and r -= alpha q with |r|^2, beta and the
+// convergence test, p = r + beta p
+int cg_iteration(lqcd_ctx* c, SWork& w, double mass, int prec, void* x, void* r, void* p, void* q, void* t) {
   const int nb = grid_for_sites(c->g.vh);
   const size_t vh = c->g.vh;
-  if (prec == 0) hipLaunchKernelGGL(k_stag_xr<0>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, q, alpha, w.partials, vh);
-  else hipLaunchKernelGGL(k_stag_xr<1>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, q, alpha, w.partials, vh);
+  CgState* st = cg_state(c);
+  LQ_TRY(stag_schur(c, prec, mass, p, t, q, w.partials, st));
+  LQ_TRY(cg_alpha(c, w.partials, nb, 0));
+  if (prec == 0) hipLaunchKernelGGL(k_stag_xr<0>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, q, st, w.partials, vh);
+  else hipLaunchKernelGGL(k_stag_xr<1>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, q, st, w.partials, vh);
+  LQ_TRY(cg_beta(c, w.partials, nb));
+  if (prec == 0) hipLaunchKernelGGL(k_stag_p<0>, dim3(nb), dim3(SBS), 0, c->stream, p, r, st, vh);
+  else hipLaunchKernelGGL(k_stag_p<1>, dim3(nb), dim3(SBS), 0, c->stream, p, r, st, vh);
   LQ_HIP(hipGetLastError());
-  return sum_pairs(c, w, nullptr, rr);
+  return LQCD_OK;
+}
+
+// CG from x, r (p is set to r) until |r| <= target or max_iters iterations
+int cg_solve(lqcd_ctx* c, SWork& w, double mass, int prec, void* x, void* r, void* p, void* q, void* t, double target,
+             int max_iters, int* iters) {
+  const int nb = grid_for_sites(c->g.vh);
+  const size_t vh = c->g.vh;
+  LQ_TRY(axpby(c, p, r, 1.0, nullptr, 0.0, prec));
+  if (prec == 0) hipLaunchKernelGGL(k_stag_dot<0>, dim3(nb), dim3(SBS), 0, c->stream, r, r, w.partials, vh);
+  else hipLaunchKernelGGL(k_stag_dot<1>, dim3(nb), dim3(SBS), 0, c->stream, r, r, w.partials, vh);
+  LQ_TRY(cg_init(c, w.partials, nb, target, max_iters));
+  return cg_run(c, [&] { return cg_iteration(c, w, mass, prec, x, r, p, q, t); }, iters);
 }
 
 int down(lqcd_ctx* c, const void* in64, void* out32) {
@@ -414,9 +437,10 @@ int accum_up(lqcd_ctx* c, void* x64, const void* e32) {
 
 }  // namespace
 
-int stag_schur(lqcd_ctx* c, int prec, double mass, const void* x_e, void* tmp_o, void* out_e, double* dot_partials) {
-  LQ_TRY(stag_hop(c, prec, 1, x_e, nullptr, 0.0, 1.0, tmp_o));                     // H_oe x
-  return stag_hop(c, prec, 0, tmp_o, x_e, mass * mass, -1.0, out_e, dot_partials);  // m^2 x - H_eo H_oe x
+int stag_schur(lqcd_ctx* c, int prec, double mass, const void* x_e, void* tmp_o, void* out_e, double* dot_partials,
+               const CgState* cg) {
+  LQ_TRY(stag_hop(c, prec, 1, x_e, nullptr, 0.0, 1.0, tmp_o, nullptr, cg));             // H_oe x
+  return stag_hop(c, prec, 0, tmp_o, x_e, mass * mass, -1.0, out_e, dot_partials, cg);  // m^2 x - H_eo H_oe x
 }
 
 int stag_solve(lqcd_ctx* c, double mass, const lqcd_solve_params& prm, const void* b_e, const void* b_o, void* x_e,
@@ -490,44 +514,15 @@ int stag_solve(lqcd_ctx* c, double mass, const lqcd_solve_params& prm, const voi
       // residual
       LQ_TRY(down(c, r, r32));
       LQ_TRY(axpby(c, e32, r32, 0.0, nullptr, 0.0, 1));
-      LQ_TRY(axpby(c, p32, r32, 1.0, nullptr, 0.0, 1));
       double rr32 = 0.0;
       LQ_TRY(dot(c, w, r32, r32, nullptr, &rr32, 1));
       const double tgt32 = std::max(delta * std::sqrt(rr32), target);
-      while (iters < prm.max_iter) {
-        LQ_TRY(stag_schur(c, 1, mass, p32, t32, q32, w.partials));
-        double pq = 0.0;
-        LQ_TRY(sum_pairs(c, w, &pq, nullptr));
-        if (!(pq > 0.0)) break;
-        const double alpha = rr32 / pq;
-        double rn = 0.0;
-        LQ_TRY(xr_update(c, w, e32, p32, r32, q32, alpha, &rn, 1));
-        ++iters;
-        if (std::sqrt(rn) <= tgt32) break;
-        LQ_TRY(axpby(c, p32, r32, 1.0, p32, rn / rr32, 1));
-        rr32 = rn;
-      }
+      LQ_TRY(cg_solve(c, w, mass, 1, e32, r32, p32, q32, t32, tgt32, prm.max_iter - iters, &iters));
       LQ_TRY(accum_up(c, x_e, e32));
       continue;
     }
-    LQ_TRY(axpby(c, p, r, 1.0));
-    const double tgt = std::min(target, 0.5 * std::sqrt(rr));
-    while (iters < prm.max_iter) {
-      LQ_TRY(stag_schur(c, 0, mass, p, t, q, w.partials));  // q = (m^2 - H_eo H_oe) p, with Re <p, q>
-      double pq = 0.0;
-      LQ_TRY(sum_pairs(c, w, &pq, nullptr));
-      if (!(pq > 0.0)) break;
-      const double alpha = rr / pq;
-      double rr_new = 0.0;
-      LQ_TRY(xr_update(c, w, x_e, p, r, q, alpha, &rr_new));
-      ++iters;
-      if (std::sqrt(rr_new) <= tgt) {
-        rr = rr_new;
-        break;
-      }
-      LQ_TRY(axpby(c, p, r, 1.0, p, rr_new / rr));
-      rr = rr_new;
-    }
+    LQ_TRY(cg_solve(c, w, mass, 0, x_e, r, p, q, t, std::min(target, 0.5 * std::sqrt(rr)), prm.max_iter - iters,
+                    &iters));
   }
   st.outer_iters = restarts;
   st.inner_iters = iters;
