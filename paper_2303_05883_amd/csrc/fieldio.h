@@ -379,13 +379,13 @@ __device__ inline void clover_apply(const void* clov, size_t i, const cx<typenam
 // (0,1)(2,3), CTRL = 0x4E swaps (0,2)(1,3) (DPP quad permutations).
 template <int CTRL>
 __device__ inline float quad_swap(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 __device__ inline double quad_swap(double v) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, true);
   return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned long long)(unsigned)lo);
 }
 // v(lane) + v(lane xor 32): the two halves of the wavefront swap values
@@ -404,6 +404,27 @@ __device__ inline double half_sum(double v) {
   const double a0 = __builtin_bit_cast(double, ((unsigned long long)(unsigned)rh[0] << 32) | (unsigned)rl[0]);
   const double a1 = __builtin_bit_cast(double, ((unsigned long long)(unsigned)rh[1] << 32) | (unsigned)rl[1]);
   return a0 + a1;
+}
+// v(lane) + v(lane xor 16): the odd and even rows of 16 lanes swap values.
+__device__ inline double row_sum(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = (int)(unsigned)(b & 0xffffffffull), hi = (int)(unsigned)(b >> 32);
+  const auto rl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto rh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  const double a0 = __builtin_bit_cast(double, ((unsigned long long)(unsigned)rh[0] << 32) | (unsigned)rl[0]);
+  const double a1 = __builtin_bit_cast(double, ((unsigned long long)(unsigned)rh[1] << 32) | (unsigned)rl[1]);
+  return a0 + a1;
+}
+// Sum over the wavefront, the same bits in every lane: exchanges inside rows of
+// 16 lanes by DPP (quad permutations 0xB1 and 0x4E, then the mirror images of 8
+// and of 16 lanes: 0x141, 0x140), then between the rows and the halves; no LDS
+// round trips.
+__device__ inline double wave_sum(double v) {
+  v += quad_swap<0xB1>(v);
+  v += quad_swap<0x4E>(v);
+  v += quad_swap<0x141>(v);
+  v += quad_swap<0x140>(v);
+  return half_sum(row_sum(v));
 }
 // Sum over the four lanes of a quad; every lane receives the total.
 template <typename T>
@@ -425,7 +446,7 @@ __device__ inline int logical_block(int remap) {
   return xcd * q + (xcd < r ? xcd : r) + idx;
 }
 
-// Deterministic block reduction of N doubles: wavefront butterfly, then the
+// Deterministic block reduction of N doubles: wavefront sums, then the
 // waves' partials summed in wave order by thread 0. Result written to out[0..N).
 template <int N>
 __device__ inline void block_reduce(double v[N], double* out) {
@@ -433,10 +454,7 @@ __device__ inline void block_reduce(double v[N], double* out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < N; ++k) {
-    double x = v[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    v[k] = x;
+    v[k] = wave_sum(v[k]);
   }
   if (lane == 0)
 #pragma unroll

@@ -5,11 +5,11 @@
 // minimal-residual block iterations, the two colours in turn; outer flexible
 // BiCGStab).
 //
-// One workgroup per block of the colour being updated, one lane per block
-// site. The lane forms the block right-hand side rho = eta - D psi at its
+// One workgroup per block of the colour being updated, two lanes per block
+// site. The lanes form the block right-hand side rho = eta - D psi at their
 // site, then the block's minimal-residual iterations run on chip: the block
-// residual and the block's internal forward links sit in LDS, q = D_B r takes
-// its neighbours from LDS, the block dot products <q, r> and <q, q> are
+// residual sits in LDS, q = D_B r takes its neighbours from LDS and its links
+// and clover blocks from registers, the block dot products <q, r> and <q, q> are
 // workgroup reductions, and psi += delta goes back to memory.
 // The right-hand side is kept up to date instead of recomputed: after a
 // colour's update its residual eta - D psi on its own sites is exactly the
@@ -52,66 +52,116 @@ struct SapArgs {
   void* psi[2];
 };
 
-// (1 -+ gamma_mu) U h-projection of a full spinor s for the hop in direction MU
-template <int MU, bool FWD>
-__device__ inline void project_any(const cx<float> s[12], cx<float> h[6]) {
-  if (MU == 3) {  // (1 - gamma_t) s = 2 (0, 0, s2, s3); (1 + gamma_t) s = 2 (s0, s1, 0, 0)
+__device__ inline void words_put(float4* L, int n, int slot, const cx<float> s[6]) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) h[k] = 2.f * s[(FWD ? 6 : 0) + k];
-  } else {
-    project<MU, FWD>(s, h);
-  }
+  for (int k = 0; k < 3; ++k) L[k * n + slot] = make_float4(s[2 * k].r, s[2 * k].i, s[2 * k + 1].r, s[2 * k + 1].i);
 }
-
-// acc += f (1 -+ gamma_mu) U s for a neighbour spinor s and link u given
-template <int MU, bool FWD>
-__device__ inline void hop_given(const cx<float> s[12], const cx<float> u[6], float f, cx<float> acc[12]) {
-  cx<float> h[6], w[6];
-  project_any<MU, FWD>(s, h);
+__device__ inline void words_get(const float4* L, int n, int slot, cx<float> s[6]) {
 #pragma unroll
-  for (int k = 0; k < 6; ++k) h[k] = f * h[k];
-  link_mul<FWD>(u, h, w);
-  expand<MU, FWD>(acc, w);
-}
-
-__device__ inline void lds_put12(float4* L, int n, int slot, const cx<float> s[12]) {
-#pragma unroll
-  for (int k = 0; k < 6; ++k) L[k * n + slot] = make_float4(s[2 * k].r, s[2 * k].i, s[2 * k + 1].r, s[2 * k + 1].i);
-}
-__device__ inline void lds_get12(const float4* L, int n, int slot, cx<float> s[12]) {
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
+  for (int k = 0; k < 3; ++k) {
     const float4 v = L[k * n + slot];
     s[2 * k] = {v.x, v.y};
     s[2 * k + 1] = {v.z, v.w};
   }
 }
-__device__ inline void lds_put6(float4* L, int n, int slot, const cx<float> u[6]) {
+
+// acc += the forward (sg = 1) or backward (sg = -1) hop in direction MU of the
+// neighbour spinor s, m = the matrix to apply (U, or U^dag for a backward hop);
+// in t, s[0..5] is the half that survives the projection and lands in the lower
+// spins (forward) or the upper ones (backward), and the projection's factor 2 is
+// in m.
+template <int MU>
+__device__ inline void pair_hop(const cx<float> s[12], const cx<float> m[9], float sg, cx<float> acc[12]) {
+  cx<float> h[6], w[6];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) L[k * n + slot] = make_float4(u[2 * k].r, u[2 * k].i, u[2 * k + 1].r, u[2 * k + 1].i);
-}
-__device__ inline void lds_get6(const float4* L, int n, int slot, cx<float> u[6]) {
+  for (int c = 0; c < 3; ++c) {
+    if (MU == 0) {  // (1 -+ gamma_mu) psi: h = u +- i sigma l
+      h[c] = s[c] + sg * mul_i(s[9 + c]);
+      h[3 + c] = s[3 + c] + sg * mul_i(s[6 + c]);
+    } else if (MU == 1) {
+      h[c] = s[c] + sg * s[9 + c];
+      h[3 + c] = s[3 + c] - sg * s[6 + c];
+    } else if (MU == 2) {
+      h[c] = s[c] + sg * mul_i(s[6 + c]);
+      h[3 + c] = s[3 + c] - sg * mul_i(s[9 + c]);
+    } else {
+      h[c] = s[c];
+      h[3 + c] = s[3 + c];
+    }
+  }
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const float4 v = L[k * n + slot];
-    u[2 * k] = {v.x, v.y};
-    u[2 * k + 1] = {v.z, v.w};
+  for (int v = 0; v < 2; ++v)
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+      w[3 * v + b] = cmadd(m[3 * b + 2], h[3 * v + 2], cmadd(m[3 * b + 1], h[3 * v + 1], m[3 * b] * h[3 * v]));
+  const float fw = sg > 0.f ? 1.f : 0.f, bw = 1.f - fw;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const cx<float> w0 = w[c], w1 = w[3 + c];
+    if (MU == 3) {
+      acc[c] = acc[c] + bw * w0;
+      acc[3 + c] = acc[3 + c] + bw * w1;
+      acc[6 + c] = acc[6 + c] + fw * w0;
+      acc[9 + c] = acc[9 + c] + fw * w1;
+      continue;
+    }
+    acc[c] = acc[c] + w0;
+    acc[3 + c] = acc[3 + c] + w1;
+    if (MU == 0) {  // lower -+= i sigma w
+      acc[6 + c] = acc[6 + c] - sg * mul_i(w1);
+      acc[9 + c] = acc[9 + c] - sg * mul_i(w0);
+    } else if (MU == 1) {
+      acc[6 + c] = acc[6 + c] - sg * w1;
+      acc[9 + c] = acc[9 + c] + sg * w0;
+    } else {
+      acc[6 + c] = acc[6 + c] - sg * mul_i(w0);
+      acc[9 + c] = acc[9 + c] + sg * mul_i(w1);
+    }
   }
 }
 
-// Sum of NV doubles over the workgroup, returned to every lane (wave
-// butterflies, then the wave sums added in wave order by every lane).
+template <int MU>
+__device__ inline void pair_hop_mem(const void* in, size_t j, const cx<float> m[9], float sg,
+                                    cx<float> acc[12]) {
+  cx<float> s[12];
+  if (MU == 3) IO<1>::load_half(in, j, sg < 0.f, s);
+  else IO<1>::load_spinor(in, j, s);
+  pair_hop<MU>(s, m, sg, acc);
+}
+template <int MU>
+__device__ inline void pair_hop_lds(const float4* Lr, int n, int slot, const cx<float> m[9], float sg,
+                                    cx<float> acc[12]) {
+  cx<float> s[12];
+  if (MU == 3) {
+    words_get(sg < 0.f ? Lr : Lr + 3 * n, n, slot, s);
+  } else {
+    words_get(Lr, n, slot, s);
+    words_get(Lr + 3 * n, n, slot, s + 6);
+  }
+  pair_hop<MU>(s, m, sg, acc);
+}
+
+// Each lane of a pair holds a partial sum of all 12 components; the forward lane
+// gets the total of the upper spins, the backward lane that of the lower ones.
+// v_permlane32_swap exchanges the backward lanes' upper with the forward lanes'
+// lower parts.
+__device__ inline void pair_total(const cx<float> p[12], cx<float> t[6]) {
+  auto one = [](float up, float lo) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(int, up), __builtin_bit_cast(int, lo), false, false);
+    return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+  };
+#pragma unroll
+  for (int k = 0; k < 6; ++k) t[k] = {one(p[k].r, p[6 + k].r), one(p[k].i, p[6 + k].i)};
+}
+
+// Sum of NV doubles over the workgroup, returned to every lane (wave sums, then
+// those added in wave order by every lane). A barrier of the caller's stands
+// between one use's reads of red and the next use's writes.
 template <int NV>
 __device__ inline void group_sum(double v[NV], double (*red)[NV]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    double x = v[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    v[k] = x;
-  }
-  __syncthreads();  // the previous use of red is over
+  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
   if (lane == 0)
 #pragma unroll
     for (int k = 0; k < NV; ++k) red[wave][k] = v[k];
@@ -125,20 +175,39 @@ __device__ inline void group_sum(double v[NV], double (*red)[NV]) {
   }
 }
 
-__global__ void __launch_bounds__(256) k_sap_block(SapArgs a) {
+// Two lanes per block site, lanes 0..31 of a wavefront with the forward hops of
+// 32 sites and lanes 32..63 with their backward ones: a lane keeps the four
+// links it needs (U, or U^dag of the backward neighbours), one chiral block of
+// A, and one half (upper or lower spins) of the residual and of delta in
+// registers through all block iterations, so an iteration reads nothing but
+// the block residual in LDS and has two barriers. Bound by vector issue (about
+// 800 instructions per lane and iteration, 230 VGPRs, 2 waves per SIMD), on
+// lattices of few blocks by the latency of one block. Against one lane per site
+// with the links in LDS and the clover term read again by every iteration (bound
+// by latency and those reads), 6 iterations, per launch: 8^3x16 blocks 4x4x2x2
+// 52 -> 23 us; 16^3x32 8x4x2x2 65 -> 42 us; 32^3x64 8x4x2x2 770 -> 504 us, 4^4
+// 1468 -> 769 us, 16x4x2x2 525 -> 515 us. Held to 128 VGPRs for 4 waves per SIMD
+// it spills (813-1227 us for the last). Blocks of fewer than 4 checkerboard
+// columns share the cache lines of a row with the next blocks, so these are
+// dealt to the XCDs in contiguous ranges (4x4x2x2 on 16^3x32 58 -> 44 us); wider
+// ones are not (8x4x2x2 on 32^3x64 533 against 553 us).
+__global__ void __launch_bounds__(512) k_sap_block(SapArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  __shared__ double red[4][3];
-  const int n = blockDim.x;  // block sites
+  __shared__ double red[8][3];
+  const int n = blockDim.x >> 1;  // block sites
   float4* Lr = reinterpret_cast<float4*>(lds_raw);  // residual, 6 words x n
-  float4* Lu = Lr + 6 * n;                          // forward links, 4 directions x 3 words x n
   const Geom& g = a.g;
   // the blockIdx-th block of this colour: rows of nb[0] blocks alternate colours
   const int hx = a.nb[0] / 2;
-  const int q = blockIdx.x % hx, row = blockIdx.x / hx;
+  const int lb = logical_block(a.b[0] < 8);
+  const int q = lb % hx, row = lb / hx;
   const int by = row % a.nb[1], bz = (row / a.nb[1]) % a.nb[2], bt = row / (a.nb[1] * a.nb[2]);
   const int bx = 2 * q + ((by + bz + bt + a.colour) & 1);
-  // this lane's site
-  const int l = threadIdx.x;
+  // this lane's site and side
+  const int h = (threadIdx.x >> 5) & 1;
+  const bool fwd = h == 0;
+  const float sg = fwd ? 1.f : -1.f;
+  const int l = ((threadIdx.x >> 6) << 5) | (threadIdx.x & 31);
   const int lx = l % a.b[0], ly = (l / a.b[0]) % a.b[1], lz = (l / (a.b[0] * a.b[1])) % a.b[2],
             lt = l / (a.b[0] * a.b[1] * a.b[2]);
   const int x = bx * a.b[0] + lx, y = by * a.b[1] + ly, z = bz * a.b[2] + lz, t = bt * a.b[3] + lt;
@@ -148,126 +217,123 @@ __global__ void __launch_bounds__(256) k_sap_block(SapArgs a) {
     return (size_t)(xx >> 1) + (size_t)lxh * (yy + (size_t)g.ly * (zz + (size_t)g.lz * tt));
   };
   const size_t i = hidx(x, y, z, t);
-  const char* gf = a.gauge + (size_t)(p * 4) * a.link_stride;        // U_mu(x), parity p
-  const char* gb = a.gauge + (size_t)((1 - p) * 4) * a.link_stride;  // U_mu(x - mu), parity 1-p
   const size_t ls = a.link_stride;
+  const char* gl = a.gauge + (size_t)((fwd ? p : 1 - p) * 4) * ls;  // forward links here, backward ones at x - mu
   const int c[4] = {x, y, z, t}, L[4] = {g.lx, g.ly, g.lz, g.lt};
   const int lc[4] = {lx, ly, lz, lt};
   const int stride[4] = {1, a.b[0], a.b[0] * a.b[1], a.b[0] * a.b[1] * a.b[2]};
+  bool in_block[4];  // the neighbour on this lane's side is in the block
+  size_t j[4];       // its checkerboard index
+  int slot[4];
+  cx<float> m[4][9];  // the matrix of this lane's hop in direction mu, scaled
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) {
+    in_block[mu] = fwd ? lc[mu] + 1 < a.b[mu] : lc[mu] > 0;
+    slot[mu] = fwd ? l + stride[mu] : l - stride[mu];
+    int d[4] = {c[0], c[1], c[2], c[3]};
+    d[mu] = fwd ? (c[mu] + 1 == L[mu] ? 0 : c[mu] + 1) : (c[mu] == 0 ? L[mu] - 1 : c[mu] - 1);
+    j[mu] = hidx(d[0], d[1], d[2], d[3]);
+    cx<float> u[6], r2[3];
+    IO<1>::template load_link<false>(gl + mu * ls, fwd ? i : j[mu], u);
+    reconstruct(u, r2);
+    // -kappa, 2 for the t projection, and the boundary factor of a hop that
+    // crosses the lattice (never inside a block) are folded in
+    const bool wrap = mu == 3 && g.t_bc < 0 && (fwd ? t + 1 == L[3] : t == 0);
+    const float f = (mu == 3 ? -2.f : -1.f) * (wrap ? -a.kappa : a.kappa);
+    const cx<float> u9[9] = {u[0], u[1], u[2], u[3], u[4], u[5], r2[0], r2[1], r2[2]};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) m[mu][k] = f * (fwd ? u9[k] : conj(u9[3 * (k % 3) + k / 3]));
+  }
 
   // ---- rho = base + kappa (H delta_other) over the hops that cross the block
   // faces (neighbours from memory; the interior hops are in base)
-  cx<float> acc[12];
+  cx<float> acc[12], r[6];
 #pragma unroll
   for (int k = 0; k < 12; ++k) acc[k] = {0.f, 0.f};
   if (a.dother[1 - p]) {
     const void* pin = a.dother[1 - p];
-#pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {
-      int f[4] = {c[0], c[1], c[2], c[3]}, bk[4] = {c[0], c[1], c[2], c[3]};
-      f[mu] = c[mu] + 1 == L[mu] ? 0 : c[mu] + 1;
-      bk[mu] = c[mu] == 0 ? L[mu] - 1 : c[mu] - 1;
-      const size_t jf = hidx(f[0], f[1], f[2], f[3]), jb = hidx(bk[0], bk[1], bk[2], bk[3]);
-      const bool ff = mu == 3 && g.t_bc < 0 && c[3] + 1 == L[3];
-      const bool fb = mu == 3 && g.t_bc < 0 && c[3] == 0;
-      const bool face_f = lc[mu] + 1 == a.b[mu], face_b = lc[mu] == 0;
-      switch (mu) {
-        case 0:
-          if (face_f) hop_dir<1, 0, true, false>(pin, gf + 0 * ls, 0, jf, i, false, acc);
-          if (face_b) hop_dir<1, 0, false, false>(pin, gb + 0 * ls, 0, jb, jb, false, acc);
-          break;
-        case 1:
-          if (face_f) hop_dir<1, 1, true, false>(pin, gf + 1 * ls, 0, jf, i, false, acc);
-          if (face_b) hop_dir<1, 1, false, false>(pin, gb + 1 * ls, 0, jb, jb, false, acc);
-          break;
-        case 2:
-          if (face_f) hop_dir<1, 2, true, false>(pin, gf + 2 * ls, 0, jf, i, false, acc);
-          if (face_b) hop_dir<1, 2, false, false>(pin, gb + 2 * ls, 0, jb, jb, false, acc);
-          break;
-        default:
-          if (face_f) hop_dir<1, 3, true, false>(pin, gf + 3 * ls, 0, jf, i, ff, acc);
-          if (face_b) hop_dir<1, 3, false, false>(pin, gb + 3 * ls, 0, jb, jb, fb, acc);
-          break;
-      }
-    }
+    if (!in_block[0]) pair_hop_mem<0>(pin, j[0], m[0], sg, acc);
+    if (!in_block[1]) pair_hop_mem<1>(pin, j[1], m[1], sg, acc);
+    if (!in_block[2]) pair_hop_mem<2>(pin, j[2], m[2], sg, acc);
+    if (!in_block[3]) pair_hop_mem<3>(pin, j[3], m[3], sg, acc);
   }
-  cx<float> r[12];
-  IO<1>::load_spinor(a.base[p], i, r);
+  {
+    cx<float> hop[6];
+    pair_total(acc, hop);
+    IO<1>::load_half(a.base[p], i, fwd, r);
 #pragma unroll
-  for (int k = 0; k < 12; ++k) r[k] = r[k] + a.kappa * acc[k];
+    for (int k = 0; k < 6; ++k) r[k] = r[k] - hop[k];
+  }
+  const bool clover = a.clov[0] != nullptr;
+  cx<float> cb[18];
+  if (clover) IO<1>::template load_clover_block<false>(a.clov[p], i, h, cb);
 
-  // ---- the block's internal forward links into LDS
-#pragma unroll
-  for (int mu = 0; mu < 4; ++mu) {
-    cx<float> u[6];
-    IO<1>::template load_link<false>(gf + mu * ls, i, u);
-    lds_put6(Lu + mu * 3 * n, n, l, u);
-  }
+  cx<float> ps[6];  // read early, added to at the end
+  IO<1>::load_half(a.psi[p], i, fwd, ps);
 
   // ---- minimal-residual iterations on the block
-  cx<float> delta[12];
+  cx<float> delta[6];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) delta[k] = {0.f, 0.f};
+  for (int k = 0; k < 6; ++k) delta[k] = {0.f, 0.f};
   for (int it = 0; it < a.nmr; ++it) {
-    __syncthreads();  // the previous residual has been read
-    lds_put12(Lr, n, l, r);
+    // the previous residual has been read: every wave has passed the barrier of
+    // the sums since
+    words_put(Lr + 3 * h * n, n, l, r);
     __syncthreads();
     // q = D_B r = A r - kappa sum of the hops that stay in the block
-    cx<float> qv[12];
-    if (a.clov[p]) clover_apply<1>(a.clov[p], i, r, qv);
-    else
+    cx<float> qv[12], qh[6];
 #pragma unroll
-      for (int k = 0; k < 12; ++k) qv[k] = r[k];
-    const float mk = -a.kappa;
-#pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {  // not unrolled: one direction's LDS data live at a time
-      cx<float> sp[12], u[6];
-      if (lc[mu] + 1 < a.b[mu]) {
-        lds_get12(Lr, n, l + stride[mu], sp);
-        lds_get6(Lu + mu * 3 * n, n, l, u);
-        switch (mu) {
-          case 0: hop_given<0, true>(sp, u, mk, qv); break;
-          case 1: hop_given<1, true>(sp, u, mk, qv); break;
-          case 2: hop_given<2, true>(sp, u, mk, qv); break;
-          default: hop_given<3, true>(sp, u, mk, qv); break;
-        }
-      }
-      if (lc[mu] > 0) {
-        lds_get12(Lr, n, l - stride[mu], sp);
-        lds_get6(Lu + mu * 3 * n, n, l - stride[mu], u);
-        switch (mu) {
-          case 0: hop_given<0, false>(sp, u, mk, qv); break;
-          case 1: hop_given<1, false>(sp, u, mk, qv); break;
-          case 2: hop_given<2, false>(sp, u, mk, qv); break;
-          default: hop_given<3, false>(sp, u, mk, qv); break;
-        }
+    for (int k = 0; k < 12; ++k) qv[k] = {0.f, 0.f};
+    if (in_block[0]) pair_hop_lds<0>(Lr, n, slot[0], m[0], sg, qv);
+    if (in_block[1]) pair_hop_lds<1>(Lr, n, slot[1], m[1], sg, qv);
+    if (in_block[2]) pair_hop_lds<2>(Lr, n, slot[2], m[2], sg, qv);
+    if (in_block[3]) pair_hop_lds<3>(Lr, n, slot[3], m[3], sg, qv);
+    if (clover) {
+      // this lane's chiral block: c_+- = u -+ l, A c added to (u, l) as (y, -+ y)
+      cx<float> o[6], ch[6], yv[6];
+      words_get(Lr + 3 * (1 - h) * n, n, l, o);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) ch[k] = fwd ? r[k] - o[k] : o[k] + r[k];
+      herm6_mul_fma(cb, ch, yv);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        qv[k] = qv[k] + yv[k];
+        qv[6 + k] = qv[6 + k] - sg * yv[k];
       }
     }
+    pair_total(qv, qh);
+    if (!clover)
+#pragma unroll
+      for (int k = 0; k < 6; ++k) qh[k] = qh[k] + r[k];
     double dv[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      const cx<float> d = cmulc(qv[k], r[k]);
+    for (int k = 0; k < 6; ++k) {
+      const cx<float> d = cmulc(qh[k], r[k]);
       dv[0] += (double)d.r;
       dv[1] += (double)d.i;
-      dv[2] += (double)qv[k].r * qv[k].r + (double)qv[k].i * qv[k].i;
+      dv[2] += (double)qh[k].r * qh[k].r + (double)qh[k].i * qh[k].i;
     }
     group_sum<3>(dv, red);
     const cx<float> alpha = dv[2] > 0.0 ? cx<float>{(float)(dv[0] / dv[2]), (float)(dv[1] / dv[2])}
                                         : cx<float>{0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
+    for (int k = 0; k < 6; ++k) {
       delta[k] = delta[k] + alpha * r[k];
-      r[k] = r[k] - alpha * qv[k];
+      r[k] = r[k] - alpha * qh[k];
     }
   }
   // ---- psi += delta on this block; the residual and delta for the next launches
-  IO<1>::store_spinor(a.res[p], i, r);
-  IO<1>::store_spinor(a.dout[p], i, delta);
-  cx<float> ps[12];
-  IO<1>::load_spinor(a.psi[p], i, ps);
+  auto store_half = [&](void* f, const cx<float> s[6]) {
+    float4* o = reinterpret_cast<float4*>(f);
 #pragma unroll
-  for (int k = 0; k < 12; ++k) ps[k] = ps[k] + delta[k];
-  IO<1>::store_spinor(a.psi[p], i, ps);
+    for (int k = 0; k < 3; ++k)
+      o[widx(i, 3 * h + k, 6)] = make_float4(s[2 * k].r, s[2 * k].i, s[2 * k + 1].r, s[2 * k + 1].i);
+  };
+  store_half(a.res[p], r);
+  store_half(a.dout[p], delta);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) ps[k] = ps[k] + delta[k];
+  store_half(a.psi[p], ps);
 }
 
 }  // namespace
@@ -320,7 +386,7 @@ int sap_apply(lqcd_ctx* c, const int b[4], int ncy, int nmr, const void* eta_e, 
   a.dout[1] = del + hb;
   LQ_TRY(blas_zero(c, 1, psi_e));
   LQ_TRY(blas_zero(c, 1, psi_o));
-  const size_t lds = (size_t)vol * (6 + 12) * 16;
+  const size_t lds = (size_t)vol * 6 * 16;
   for (int cy = 0; cy < ncy; ++cy)
     for (int colour = 0; colour < 2; ++colour) {
       a.colour = colour;
@@ -332,7 +398,7 @@ int sap_apply(lqcd_ctx* c, const int b[4], int ncy, int nmr, const void* eta_e, 
       const bool none = cy == 0 && colour == 0;
       a.dother[0] = none ? nullptr : del;
       a.dother[1] = none ? nullptr : del + hb;
-      hipLaunchKernelGGL(k_sap_block, dim3(nblocks / 2), dim3(vol), lds, c->stream, a);
+      hipLaunchKernelGGL(k_sap_block, dim3(nblocks / 2), dim3(2 * vol), lds, c->stream, a);
     }
   LQ_HIP(hipGetLastError());
   return LQCD_OK;
