@@ -68,14 +68,15 @@ __global__ void __launch_bounds__(BS) k_bblas(BBlasArgs b) {
     const size_t i = (size_t)blk * BS + threadIdx.x;
     const bool act = i < vh;
     if (OP == B_P_UPDATE) {
-      if (act) p_update_site<P>(S.f[F_R], S.f[F_P], S.f[F_V], S.sc, i);
+      if (act) p_update_site<P>(S.f[F_R], S.f[F_P], S.f[F_V], {S.sc->beta_r, S.sc->beta_i}, {S.sc->omega_r, S.sc->omega_i}, i);
     } else if (OP == B_S_UPDATE) {
-      if (act) s_update_site<P>(S.f[F_R], S.f[F_V], S.f[F_S], S.sc, i);
+      if (act) s_update_site<P>(S.f[F_R], S.f[F_V], S.f[F_S], {S.sc->alpha_r, S.sc->alpha_i}, i);
     } else {
       double red[3] = {0.0, 0.0, 0.0};
       if (OP == B_XR_UPDATE) {
         if (act)
-          xr_update_site<P, PX>(S.f[F_X], S.f[F_P], S.f[F_S], S.f[F_T], S.f[F_R], S.f[F_RHAT], S.sc, i, red);
+          xr_update_site<P, PX>(S.f[F_X], S.f[F_P], S.f[F_S], S.f[F_T], S.f[F_R], S.f[F_RHAT],
+                                {S.sc->alpha_r, S.sc->alpha_i}, {S.sc->omega_r, S.sc->omega_i}, i, red);
       } else {  // start: rhat = p = r, <rhat, r>, <r, r>
         if (act) {
           copy_site<P>(S.f[F_R], S.f[F_RHAT], i);

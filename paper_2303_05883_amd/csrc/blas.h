@@ -18,14 +18,29 @@ struct Scal {
   int breakdown;
   int iters;        // iterations since the last (re)start
   int max_iters;
-  double pad[2];
+  double next_r, next_i;  // rho as the direction update formed it; rho itself follows in the s update (see Fold)
 };
 
+// The partial sums of a reduction that the vector update after it is to add by
+// itself (n records), or none (n = 0: a finalize kernel has done it). Every
+// workgroup adds all records in the same order and forms the scalar for itself;
+// workgroup 0 writes what later launches read, never what its own launch reads:
+// the direction update reads rho and leaves the new one in next, the s update
+// of the next iteration reads next and writes rho.
+struct Fold {
+  const double* partials = nullptr;
+  int n = 0;
+};
+// Whether n records are folded: up to 1536 (36 KB from L2 per workgroup and
+// about 1.5 us) that is cheaper than a one-block launch (about 4 us and the gap
+// before the next one); beyond, the reads of all workgroups add up.
+inline bool fold_ok(int n) { return n <= 1536; }
+
 int blas_blocks(size_t vh);
-int blas_p_update(lqcd_ctx* c, int prec, const void* r, void* p, const void* v, const Scal* sc);
-int blas_s_update(lqcd_ctx* c, int prec, const void* r, const void* v, void* s, const Scal* sc);
+int blas_p_update(lqcd_ctx* c, int prec, const void* r, void* p, const void* v, Scal* sc, Fold f = Fold());
+int blas_s_update(lqcd_ctx* c, int prec, const void* r, const void* v, void* s, Scal* sc, Fold f = Fold());
 int blas_xr_update(lqcd_ctx* c, int prec, int xprec, void* x, const void* p, const void* s, const void* t, void* r,
-                   const void* rhat, const Scal* sc, double* partials);
+                   const void* rhat, Scal* sc, double* partials, Fold f = Fold());
 int blas_dot_norm(lqcd_ctx* c, int prec, const void* a, const void* b, double* partials);
 int blas_sub_norm(lqcd_ctx* c, const void* a, const void* b, void* out, double* partials);
 int blas_scale_down(lqcd_ctx* c, int dprec, const void* src, void* dst, const double* dscale, double hscale);

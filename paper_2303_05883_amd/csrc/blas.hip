@@ -4,9 +4,9 @@
 // device memory, so an iteration needs no host round trip and can be replayed
 // from a captured graph; every kernel first checks the solve's "done" flag and
 // returns at once when it is set. Reductions are FP64: each block writes its
-// partial sums in a fixed slot, and a one-block finalize kernel adds them in a
-// fixed order, so repeated FP64 runs are bitwise identical. The finalize
-// kernels also compute the next scalars (the solver's global reductions, of up
+// partial sums in a fixed slot, and a one-block finalize kernel, or on small
+// lattices the next update kernel itself (Fold), adds them in a fixed order, so
+// repeated FP64 runs are bitwise identical. They also compute the next scalars (the solver's global reductions, of up
 // to three values at once, the pattern the paper credits for solver
 // efficiency in Sec. 3).
 #include "blascore.h"
@@ -18,32 +18,76 @@ namespace {
 constexpr int BS = 256;
 constexpr int FBS = 1024;  // threads of the one-block finalize kernels
 
-__device__ inline bool is_done(const Scal* s) { return s && s->done; }
-
-// p = r + beta (p - omega v)
-template <int P>
-__global__ void __launch_bounds__(BS) k_p_update(const void* r, void* p, const void* v, const Scal* sc, size_t vh) {
-  if (is_done(sc)) return;
-  const size_t i = (size_t)blockIdx.x * BS + threadIdx.x;
-  if (i < vh) p_update_site<P>(r, p, v, sc, i);
+__device__ inline bool is_done(const Scal* s) {
+  return s && __hip_atomic_load(&s->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
 
-// s = r - alpha v
+// p = r + beta (p - omega v); with f, after forming beta from the sums of <rhat, r>, <r, r>
 template <int P>
-__global__ void __launch_bounds__(BS) k_s_update(const void* r, const void* v, void* s, const Scal* sc, size_t vh) {
+__global__ void __launch_bounds__(BS) k_p_update(const void* r, void* p, const void* v, Scal* sc, Fold f, size_t vh) {
   if (is_done(sc)) return;
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  cx<double> beta = {sc->beta_r, sc->beta_i};
+  if (f.n) {
+    double s[3];
+    sum_partials<3>(f.partials, f.n, s);
+    const int end = beta_of(sc, s, beta);
+    if (lead) {
+      sc->next_r = s[0];
+      sc->next_i = s[1];
+      scal_count(sc, s[2], end);
+    }
+    if (end) return;
+  }
   const size_t i = (size_t)blockIdx.x * BS + threadIdx.x;
-  if (i < vh) s_update_site<P>(r, v, s, sc, i);
+  if (i < vh) p_update_site<P>(r, p, v, beta, {sc->omega_r, sc->omega_i}, i);
 }
 
-// x += alpha p + omega s (x in precision PX); r = s - omega t; partials <rhat, r>, <r, r>
+// s = r - alpha v; with f, after forming alpha from the sums of <rhat, v>
+template <int P>
+__global__ void __launch_bounds__(BS) k_s_update(const void* r, const void* v, void* s, Scal* sc, Fold f, size_t vh) {
+  if (is_done(sc)) return;
+  cx<double> alpha = {sc->alpha_r, sc->alpha_i};
+  if (f.n) {
+    const cx<double> rho = {sc->next_r, sc->next_i};
+    double d[2];
+    sum_partials<2>(f.partials, f.n, d);
+    const bool ok = alpha_of(rho, d, alpha);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      sc->rho_r = rho.r;
+      sc->rho_i = rho.i;
+      if (ok) {
+        sc->alpha_r = alpha.r;
+        sc->alpha_i = alpha.i;
+      } else {
+        scal_stop(sc, true);
+      }
+    }
+    if (!ok) return;
+  }
+  const size_t i = (size_t)blockIdx.x * BS + threadIdx.x;
+  if (i < vh) s_update_site<P>(r, v, s, alpha, i);
+}
+
+// x += alpha p + omega s (x in precision PX); r = s - omega t; partials <rhat, r>, <r, r>;
+// with f, after forming omega from the sums of <t, s>, <t, t>
 template <int P, int PX>
 __global__ void __launch_bounds__(BS) k_xr_update(void* x, const void* p, const void* s, const void* t, void* r,
-                                                  const void* rhat, const Scal* sc, double* partials, size_t vh) {
+                                                  const void* rhat, Scal* sc, Fold f, double* partials, size_t vh) {
   if (is_done(sc)) return;
+  cx<double> omega = {sc->omega_r, sc->omega_i};
+  if (f.n) {
+    double d[3];
+    sum_partials<3>(f.partials, f.n, d);
+    omega = omega_of(d);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      sc->omega_r = omega.r;
+      sc->omega_i = omega.i;
+    }
+  }
   const size_t i = (size_t)blockIdx.x * BS + threadIdx.x;
   double red[3] = {0.0, 0.0, 0.0};
-  if (i < vh) xr_update_site<P, PX>(x, p, s, t, r, rhat, sc, i, red);
+  if (i < vh) xr_update_site<P, PX>(x, p, s, t, r, rhat, {sc->alpha_r, sc->alpha_i}, omega, i, red);
   block_reduce<3>(red, partials + (size_t)blockIdx.x * 3);
 }
 
@@ -203,32 +247,32 @@ int blas_blocks(size_t vh) { return nblk(vh); }
     default: return set_error(LQCD_EINVAL, "bad precision");   \
   }
 
-int blas_p_update(lqcd_ctx* c, int prec, const void* r, void* p, const void* v, const Scal* sc) {
+int blas_p_update(lqcd_ctx* c, int prec, const void* r, void* p, const void* v, Scal* sc, Fold f) {
   const size_t vh = c->g.vh;
-  LQ_PREC_SWITCH(prec, hipLaunchKernelGGL(k_p_update<P>, dim3(nblk(vh)), dim3(BS), 0, c->stream, r, p, v, sc, vh));
+  LQ_PREC_SWITCH(prec, hipLaunchKernelGGL(k_p_update<P>, dim3(nblk(vh)), dim3(BS), 0, c->stream, r, p, v, sc, f, vh));
   LQ_HIP(hipGetLastError());
   return LQCD_OK;
 }
 
-int blas_s_update(lqcd_ctx* c, int prec, const void* r, const void* v, void* s, const Scal* sc) {
+int blas_s_update(lqcd_ctx* c, int prec, const void* r, const void* v, void* s, Scal* sc, Fold f) {
   const size_t vh = c->g.vh;
-  LQ_PREC_SWITCH(prec, hipLaunchKernelGGL(k_s_update<P>, dim3(nblk(vh)), dim3(BS), 0, c->stream, r, v, s, sc, vh));
+  LQ_PREC_SWITCH(prec, hipLaunchKernelGGL(k_s_update<P>, dim3(nblk(vh)), dim3(BS), 0, c->stream, r, v, s, sc, f, vh));
   LQ_HIP(hipGetLastError());
   return LQCD_OK;
 }
 
 int blas_xr_update(lqcd_ctx* c, int prec, int xprec, void* x, const void* p, const void* s, const void* t, void* r,
-                   const void* rhat, const Scal* sc, double* partials) {
+                   const void* rhat, Scal* sc, double* partials, Fold f) {
   const size_t vh = c->g.vh;
   const dim3 g(nblk(vh)), b(BS);
   if (prec == 0 && xprec == 0)
-    hipLaunchKernelGGL((k_xr_update<0, 0>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, partials, vh);
+    hipLaunchKernelGGL((k_xr_update<0, 0>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, f, partials, vh);
   else if (prec == 1 && xprec == 1)
-    hipLaunchKernelGGL((k_xr_update<1, 1>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, partials, vh);
+    hipLaunchKernelGGL((k_xr_update<1, 1>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, f, partials, vh);
   else if (prec == 2 && xprec == 1)
-    hipLaunchKernelGGL((k_xr_update<2, 1>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, partials, vh);
+    hipLaunchKernelGGL((k_xr_update<2, 1>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, f, partials, vh);
   else if (prec == 2 && xprec == 2)
-    hipLaunchKernelGGL((k_xr_update<2, 2>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, partials, vh);
+    hipLaunchKernelGGL((k_xr_update<2, 2>), g, b, 0, c->stream, x, p, s, t, r, rhat, sc, f, partials, vh);
   else
     return set_error(LQCD_EINVAL, "unsupported precision pair for x/r update");
   LQ_HIP(hipGetLastError());

@@ -8,16 +8,18 @@
 
 namespace lq {
 
+// A complex scalar in double, and as the fields' type
 template <typename T>
-__device__ inline cx<T> ld_scalar(const double* re_im) {
-  return {(T)re_im[0], (T)re_im[1]};
+__device__ inline cx<T> as(cx<double> z) {
+  return {(T)z.r, (T)z.i};
 }
 
 // p = r + beta (p - omega v)
 template <int P>
-__device__ inline void p_update_site(const void* r, void* p, const void* v, const Scal* sc, size_t i) {
+__device__ inline void p_update_site(const void* r, void* p, const void* v, cx<double> beta_d, cx<double> omega_d,
+                                     size_t i) {
   using T = typename IO<P>::T;
-  const cx<T> beta = ld_scalar<T>(&sc->beta_r), omega = ld_scalar<T>(&sc->omega_r);
+  const cx<T> beta = as<T>(beta_d), omega = as<T>(omega_d);
   cx<T> a[12], b[12], c[12];
   IO<P>::load_spinor(r, i, a);
   IO<P>::load_spinor(p, i, b);
@@ -29,9 +31,9 @@ __device__ inline void p_update_site(const void* r, void* p, const void* v, cons
 
 // s = r - alpha v
 template <int P>
-__device__ inline void s_update_site(const void* r, const void* v, void* s, const Scal* sc, size_t i) {
+__device__ inline void s_update_site(const void* r, const void* v, void* s, cx<double> alpha_d, size_t i) {
   using T = typename IO<P>::T;
-  const cx<T> alpha = ld_scalar<T>(&sc->alpha_r);
+  const cx<T> alpha = as<T>(alpha_d);
   cx<T> a[12], c[12];
   IO<P>::load_spinor(r, i, a);
   IO<P>::load_spinor(v, i, c);
@@ -43,11 +45,11 @@ __device__ inline void s_update_site(const void* r, const void* v, void* s, cons
 // x += alpha p + omega s (x in precision PX); r = s - omega t; red += <rhat, r>, <r, r>
 template <int P, int PX>
 __device__ inline void xr_update_site(void* x, const void* p, const void* s, const void* t, void* r, const void* rhat,
-                                      const Scal* sc, size_t i, double red[3]) {
+                                      cx<double> alpha_d, cx<double> omega_d, size_t i, double red[3]) {
   using T = typename IO<P>::T;
   using TX = typename IO<PX>::T;
-  const cx<T> omega = ld_scalar<T>(&sc->omega_r);
-  const cx<TX> alx = ld_scalar<TX>(&sc->alpha_r), omx = ld_scalar<TX>(&sc->omega_r);
+  const cx<T> omega = as<T>(omega_d);
+  const cx<TX> alx = as<TX>(alpha_d), omx = as<TX>(omega_d);
   cx<T> pv[12], sv[12], tv[12];
   cx<TX> xv[12];
   IO<P>::load_spinor(p, i, pv);
@@ -148,52 +150,80 @@ __device__ inline void sum_partials(const double* partials, int n, double out[W]
   __syncthreads();
 }
 
-// The scalar updates of one BiCGStab (thread 0 of the block calls them).
+// The scalar updates of one BiCGStab. *_of form the values from the sums v (any
+// thread may), scal_* store them (one thread).
+// alpha = rho / <rhat, v>; false when <rhat, v> vanishes
+__device__ inline bool alpha_of(cx<double> rho, const double v[2], cx<double>& alpha) {
+  if (v[0] == 0.0 && v[1] == 0.0) return false;
+  cdiv(rho.r, rho.i, v[0], v[1], alpha.r, alpha.i);
+  return true;
+}
+
+__device__ inline void scal_stop(Scal* sc, bool breakdown) {
+  if (breakdown) sc->breakdown = 1;
+  __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ inline void scal_alpha(Scal* sc, const double v[2]) {
-  if (v[0] == 0.0 && v[1] == 0.0) {
-    sc->breakdown = 1;
-    sc->done = 1;
+  cx<double> a;
+  if (!alpha_of({sc->rho_r, sc->rho_i}, v, a)) {
+    scal_stop(sc, true);
     return;
   }
-  cdiv(sc->rho_r, sc->rho_i, v[0], v[1], sc->alpha_r, sc->alpha_i);
+  sc->alpha_r = a.r;
+  sc->alpha_i = a.i;
+}
+
+// omega = <t, s> / <t, t>
+__device__ inline cx<double> omega_of(const double v[3]) {
+  if (v[2] == 0.0) return {0.0, 0.0};
+  return {v[0] / v[2], v[1] / v[2]};
 }
 
 __device__ inline void scal_omega(Scal* sc, const double v[3]) {
-  if (v[2] == 0.0) {
-    sc->omega_r = 0.0;
-    sc->omega_i = 0.0;
-  } else {
-    sc->omega_r = v[0] / v[2];
-    sc->omega_i = v[1] / v[2];
-  }
+  const cx<double> w = omega_of(v);
+  sc->omega_r = w.r;
+  sc->omega_i = w.i;
 }
 
-__device__ inline void scal_rho(Scal* sc, const double v[3]) {
-  sc->iters += 1;
-  sc->rr = v[2];
-  if (v[2] <= sc->target2 || !(v[2] == v[2])) {
-    sc->done = 1;
-    if (!(v[2] == v[2])) sc->breakdown = 1;
-    return;
-  }
-  if ((v[0] == 0.0 && v[1] == 0.0) || (sc->omega_r == 0.0 && sc->omega_i == 0.0)) {
-    sc->breakdown = 1;
-    sc->done = 1;
-    return;
-  }
+// rho_new = <rhat, r>, rr = <r, r>: beta = (rho_new / rho)(alpha / omega), or why
+// the iteration ends: 1 converged, 2 broken down
+__device__ inline int beta_of(const Scal* sc, const double v[3], cx<double>& beta) {
+  beta = {0.0, 0.0};
+  if (!(v[2] == v[2])) return 2;
+  if (v[2] <= sc->target2) return 1;
+  if ((v[0] == 0.0 && v[1] == 0.0) || (sc->omega_r == 0.0 && sc->omega_i == 0.0)) return 2;
   double qr, qi, ar, ai;
   cdiv(v[0], v[1], sc->rho_r, sc->rho_i, qr, qi);
   cdiv(sc->alpha_r, sc->alpha_i, sc->omega_r, sc->omega_i, ar, ai);
-  sc->beta_r = qr * ar - qi * ai;
-  sc->beta_i = qr * ai + qi * ar;
-  sc->rho_r = v[0];
-  sc->rho_i = v[1];
-  if (sc->iters >= sc->max_iters) sc->done = 1;
+  beta = cx<double>{qr, qi} * cx<double>{ar, ai};
+  return 0;
+}
+
+// the count and the end of an iteration; end as beta_of returns it
+__device__ inline void scal_count(Scal* sc, double rr, int end) {
+  sc->iters += 1;
+  sc->rr = rr;
+  if (end || sc->iters >= sc->max_iters) scal_stop(sc, end == 2);
+}
+
+__device__ inline void scal_rho(Scal* sc, const double v[3]) {
+  cx<double> beta;
+  const int end = beta_of(sc, v, beta);
+  if (!end) {
+    sc->beta_r = beta.r;
+    sc->beta_i = beta.i;
+    sc->rho_r = v[0];
+    sc->rho_i = v[1];
+    sc->next_r = v[0];
+    sc->next_i = v[1];
+  }
+  scal_count(sc, v[2], end);
 }
 
 __device__ inline void scal_init(Scal* sc, const double v[3], double target2, int max_iters) {
-  sc->rho_r = v[0];
-  sc->rho_i = v[1];
+  sc->rho_r = sc->next_r = v[0];
+  sc->rho_i = sc->next_i = v[1];
   sc->rr = v[2];
   sc->alpha_r = 1.0;
   sc->alpha_i = 0.0;
@@ -211,8 +241,8 @@ __device__ inline void scal_init(Scal* sc, const double v[3], double target2, in
 // After a reliable update replaced r: rho = <rhat, r>, rr = <r, r>, new
 // target; alpha, omega and the iteration count carry on.
 __device__ inline void scal_reliable(Scal* sc, const double v[3], double target2) {
-  sc->rho_r = v[0];
-  sc->rho_i = v[1];
+  sc->rho_r = sc->next_r = v[0];
+  sc->rho_i = sc->next_i = v[1];
   sc->rr = v[2];
   sc->target2 = target2;
   sc->breakdown = 0;

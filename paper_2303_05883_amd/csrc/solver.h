@@ -13,7 +13,8 @@ struct InnerVecs {
   void *r = nullptr, *rhat = nullptr, *pv = nullptr, *v_ = nullptr, *s = nullptr, *t = nullptr, *y = nullptr,
        *x = nullptr;
   Scal* sc = nullptr;
-  double* partials = nullptr;
+  double* partials = nullptr;     // of <rhat, v>, then of <rhat, r>, <r, r>
+  double* partials_ts = nullptr;  // of <t, s>, <t, t> (in the same allocation)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int graph_k = 0, graph_block = 0, graph_remap = -1, graph_nt = -1, graph_split = -1;

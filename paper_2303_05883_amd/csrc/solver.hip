@@ -46,7 +46,8 @@ int InnerVecs::init(lqcd_ctx* c, int p, int xp) {
   LQ_TRY(alloc(&x, spinor_bytes(xprec, vh)));
   LQ_TRY(alloc(reinterpret_cast<void**>(&sc), sizeof(Scal)));
   const size_t np = std::max((size_t)blas_blocks(vh), max_hop_blocks(vh)) * 3;
-  LQ_TRY(alloc(reinterpret_cast<void**>(&partials), np * sizeof(double)));
+  LQ_TRY(alloc(reinterpret_cast<void**>(&partials), 2 * np * sizeof(double)));
+  partials_ts = partials + np;
   return LQCD_OK;
 }
 
@@ -128,14 +129,20 @@ static int bicg_iteration(lqcd_ctx* c, InnerVecs& v) {
   const int P = v.prec;
   const int* skip = &v.sc->done;
   int nb = 0;
+  // small lattices: the update kernels add the reductions' records themselves,
+  // 7 launches per iteration instead of 10
   LQ_TRY(op_schur(c, P, v.pv, v.v_, v.y, RED_DOT, v.rhat, v.partials, skip, &nb));
-  LQ_TRY(fin_alpha(c, v.sc, v.partials, nb));
-  LQ_TRY(blas_s_update(c, P, v.r, v.v_, v.s, v.sc));
-  LQ_TRY(op_schur(c, P, v.s, v.t, v.y, RED_TS, nullptr, v.partials, skip, &nb));
-  LQ_TRY(fin_omega(c, v.sc, v.partials, nb));
-  LQ_TRY(blas_xr_update(c, P, v.xprec, v.x, v.pv, v.s, v.t, v.r, v.rhat, v.sc, v.partials));
-  LQ_TRY(fin_rho(c, v.sc, v.partials, blas_blocks(c->g.vh)));
-  return blas_p_update(c, P, v.r, v.pv, v.v_, v.sc);
+  const int nr = blas_blocks(c->g.vh);
+  const bool fold = fold_ok(nb) && fold_ok(nr);
+  const Fold none, ds = fold ? Fold{v.partials, nb} : none, dt = fold ? Fold{v.partials_ts, nb} : none,
+                   dr = fold ? Fold{v.partials, nr} : none;
+  if (!fold) LQ_TRY(fin_alpha(c, v.sc, v.partials, nb));
+  LQ_TRY(blas_s_update(c, P, v.r, v.v_, v.s, v.sc, ds));
+  LQ_TRY(op_schur(c, P, v.s, v.t, v.y, RED_TS, nullptr, v.partials_ts, skip, &nb));
+  if (!fold) LQ_TRY(fin_omega(c, v.sc, v.partials_ts, nb));
+  LQ_TRY(blas_xr_update(c, P, v.xprec, v.x, v.pv, v.s, v.t, v.r, v.rhat, v.sc, v.partials, dt));
+  if (!fold) LQ_TRY(fin_rho(c, v.sc, v.partials, nr));
+  return blas_p_update(c, P, v.r, v.pv, v.v_, v.sc, dr);
 }
 
 static int run_chunk(lqcd_ctx* c, InnerVecs& v, int k, bool use_graph) {
