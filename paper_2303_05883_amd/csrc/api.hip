@@ -195,6 +195,7 @@ int lqcd_create(const int dims[4], int t_bc, void* hip_stream, lqcd_ctx** out) {
   if (s == LQCD_OK) s = dalloc(reinterpret_cast<void**>(&c->dscal), 64 * sizeof(double));
   if (s == LQCD_OK && hipHostMalloc(reinterpret_cast<void**>(&c->hscal), 64 * sizeof(double)) != hipSuccess)
     s = set_error(LQCD_ENOMEM, "hipHostMalloc failed");
+  for (int p = 0; p < 3; ++p) default_hop_shape(c->g, p, c->hop_block[p], c->hop_split[p], c->hop_remap[p], c->hop_nt[p]);
   if (s == LQCD_OK) s = tune_load_defaults(c);
   if (s != LQCD_OK) {
     lqcd_destroy(c);

@@ -542,6 +542,51 @@ bool march_shape_ok(const Geom& g, int prec, int block, int zc) {
   return march_lds_bytes(g, prec, ty) <= 158 * 1024;  // with the reduction scratch, within gfx950's 160 KiB
 }
 
+// The launch shape a context starts with, by the sites per parity (vh) and the
+// precision; the tune cache, lqcd_autotune and lqcd_set_hop_shape replace it.
+// Measured per Schur operator (two hops) in us, clover, against one lane per
+// site in workgroups of 256 in site order:
+//   vh <= 12000: the launch is one chain of loads; four lanes per site shorten it
+//     (8^4 FP64 20.0 -> 12.0, FP32 16.2 -> 10.6, FP16 15.2 -> 11.2);
+//   vh <= 40000: two lanes per site (16^4 FP64 28.4 -> 25.6, FP32 21.6 -> 16.2,
+//     FP16 15.6 -> 13.8, which is bound by vector issue from about 33000 on);
+//   FP32 up to 120000: two lanes (16^3x32 25.9 -> 23.8); up to 250000 one lane has
+//     enough waves and fewer instructions (24^4 50.0, two lanes 53.9); beyond,
+//     neighbours in flight per XCD count and two lanes win (24^3x48 124.6 -> 110.6);
+//   FP64 from 140000 on: two lanes (24^4 124 -> 113); from 250000 on the links are
+//     streamed past the caches (24^3x48 265 -> 236), with one lane where no z
+//     slabs fit (30x22x26x38 246 -> 229, two lanes 239) and from 450000 on
+//     (32^3x64 775 -> 700, two lanes 711);
+//   large lattices whose lz is a multiple of 8: XCD z slabs (32^3x64 FP32 391 -> 364,
+//     in site order 389; FP16 205 -> 185, from 800000 on).
+void default_hop_shape(const Geom& g, int prec, int& block, int& split, int& remap, int& nt) {
+  const int vh = g.vh;
+  const bool slabs = g.lz % 8 == 0;
+  block = 256;
+  split = 1;
+  remap = 1;
+  nt = 0;
+  if (vh <= 12000) {
+    block = 64;
+    split = 4;
+  } else if (vh <= (prec == 2 ? 33000 : 40000)) {
+    block = prec == 0 ? 64 : 256;
+    split = 2;
+  } else if (prec == 0 && vh > 140000) {
+    nt = vh > 250000;
+    remap = nt && slabs ? 2 : 1;
+    split = !nt || (slabs && vh < 450000) ? 2 : 1;
+    if (!nt) block = 64;
+  } else if (prec == 1) {
+    nt = vh > 450000;
+    remap = nt && slabs ? 2 : 1;
+    split = vh <= 120000 || vh > 250000 ? 2 : 1;
+  } else if (prec == 2 && vh > 800000) {
+    nt = 1;
+    remap = slabs ? 2 : 1;
+  }
+}
+
 int hop_blocks(lqcd_ctx* c, int prec) {
   if (c->hop_split[prec] == 0) {  // plane march: block = Lx/2 x rows lanes, hop_remap = z planes per block
     const int ty = c->hop_block[prec] / c->g.lxh;

@@ -135,7 +135,7 @@ struct lqcd_ctx {
   double* dscal = nullptr;     // device scalars for small results
   double* hscal = nullptr;     // pinned host mirror
 
-  // launch shape of the hop per precision (autotuned)
+  // launch shape of the hop per precision (default_hop_shape, the tune cache or autotuned)
   int hop_block[3] = {256, 256, 256};
   int hop_remap[3] = {1, 1, 1};
   int hop_nt[3] = {0, 0, 0};     // non-temporal link loads
@@ -214,6 +214,7 @@ inline int log_level() {
 }
 
 int hop_blocks(lqcd_ctx* c, int prec);
+void default_hop_shape(const Geom& g, int prec, int& block, int& split, int& remap, int& nt);
 // Whether (block lanes, zc planes) is a valid plane-march shape on this lattice.
 bool march_shape_ok(const Geom& g, int prec, int block, int zc);
 // most blocks any hop launch shape uses (partials buffers are sized for it)
