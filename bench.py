@@ -212,7 +212,7 @@ def measured_traffic(prec_name, path=TRAFFIC_FILE, sources=KERNEL_SOURCES, kerne
         return None
     for ln in lines:
         if ln.startswith(prec_name + ":"):
-            if kernel is not None and f"lq::{kernel}<" not in ln and f" {kernel}<" not in ln:
+            if kernel is not None and not any(f"{pre}{kernel}{end}" in ln for pre in ("lq::", " ") for end in "<,"):
                 return None
             parts = ln.split()
             return int(parts[parts.index("traffic_bytes") + 1])
@@ -370,14 +370,14 @@ def roofline_of(torch, lat, lqcd, dom, vh, U=None, kappa=None, csw=None):
     log(f"hop kernel: {hop}")
     pd = 1 if dom == "f32" else 2
     block, split, xmap, nt = lat.get_hop_shape(pd)
-    kname = {1: "k_hop", 2: "k_hop2", 4: "k_hop4", 0: "k_hopz"}[split]
+    kname = "k_hopz" if split == 0 else f"k_hop<{split}"  # as the profiler names it, up to the next argument
     shape = ({"lanes": block, "z_planes_per_block": xmap} if split == 0 else
              {"block": block, "lanes_per_site": split, "xcd_map": xmap})
     shape["nt_links"] = nt
     roof = {"bound": "hbm", "achieved": hop[dom]["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": hop[dom]["frac_hbm"],
             "traffic": measured_traffic(dom, kernel=kname) if tuple(lat.dims) == DIMS else None,
-            "kernel": f"{kname}<{pd},EPI_SCALE> (Dslash, {dom} storage)", "launch_shape": shape,
+            "kernel": f"{kname}{'<' if split == 0 else ','}{pd},EPI_SCALE> (Dslash, {dom} storage)", "launch_shape": shape,
             "bytes_per_launch": HOP_BYTES[pd] * vh}
     if U is not None and tuple(lat.dims) == DIMS:
         ms = time_hop_rotated(torch, lqcd, lat, U, kappa, csw, pd)

@@ -461,9 +461,10 @@ int lqcd_autotune(lqcd_ctx* ctx, int prec, const char* path);
  * lanes = (Lx/2) x rows (rows dividing Ly, at most 512 lanes), xcd_map = z
  * planes per workgroup (dividing Lz).
  * nt = 1 to load the links non-temporally. EINVAL for any shape that is not
- * valid on this lattice. The results do not depend on the shape beyond the
- * rounding of the order in which the hops of a site and the fused reductions
- * are added. */
+ * valid on this lattice. The full operator D, both parities in one launch, has a
+ * shape of its own that follows the lattice alone. The results do not depend on
+ * the shape beyond the rounding of the order in which the hops of a site and
+ * the fused reductions are added. */
 int lqcd_set_hop_shape(lqcd_ctx* ctx, int prec, int block, int split, int xcd_map, int nt);
 /* The launch shape in use for one precision (as lqcd_set_hop_shape takes it);
  * any output pointer may be NULL. */

@@ -306,28 +306,38 @@ int lqcd_set_clover(lqcd_ctx* c, double kappa, double csw) {
   return LQCD_OK;
 }
 
-static int apply_halves(lqcd_ctx* c, int op, int prec, void* in_e, void* in_o, void* out_e, void* out_o,
-                        bool* write_e, bool* write_o) {
-  const double k = c->kappa;
-  *write_e = *write_o = true;
+// op on half fields: the parities it reads (bit p: parity p)
+static int parities_read(int op) {
   switch (op) {
-    case LQCD_D: return op_full(c, prec, in_e, in_o, out_e, out_o);
-    case LQCD_DEE: *write_o = false; return launch_site(c, prec, clover_slot(c, prec, 0), in_e, out_e);
-    case LQCD_DOO: *write_e = false; return launch_site(c, prec, clover_slot(c, prec, 1), in_o, out_o);
-    case LQCD_DEE_INV: *write_o = false; return launch_site(c, prec, clover_slot(c, prec, 2), in_e, out_e);
-    case LQCD_DOO_INV: *write_e = false; return launch_site(c, prec, clover_slot(c, prec, 3), in_o, out_o);
-    case LQCD_DEO: *write_o = false; return op_hop(c, prec, 0, in_o, out_e, -k);
-    case LQCD_DOE: *write_e = false; return op_hop(c, prec, 1, in_e, out_o, -k);
-    case LQCD_HOP_EO: *write_o = false; return op_hop(c, prec, 0, in_o, out_e, 1.0);
-    case LQCD_HOP_OE: *write_e = false; return op_hop(c, prec, 1, in_e, out_o, 1.0);
-    case LQCD_DPREC_SCHUR:
-      *write_o = false;
-      return op_schur(c, prec, in_e, out_e, out_o, RED_NONE, nullptr, nullptr, nullptr, nullptr);
+    case LQCD_D: return 3;
+    case LQCD_DOO: case LQCD_DOO_INV: case LQCD_DEO: case LQCD_HOP_EO: return 2;
+  }
+  return 1;
+}
+
+// The operators that write one parity, in from the half fields in[2], the result in
+// *out (one of tmp[2]) with its parity
+static int apply_half(lqcd_ctx* c, int op, int prec, void* const in[2], void* const tmp[2], void** out, int* parity) {
+  const double k = c->kappa;
+  *out = tmp[0];
+  *parity = 0;
+  switch (op) {
+    case LQCD_DEE: return launch_site(c, prec, clover_slot(c, prec, 0), in[0], *out);
+    case LQCD_DEE_INV: return launch_site(c, prec, clover_slot(c, prec, 2), in[0], *out);
+    case LQCD_DEO: return op_hop(c, prec, 0, in[1], *out, -k);
+    case LQCD_HOP_EO: return op_hop(c, prec, 0, in[1], *out, 1.0);
+    case LQCD_DPREC_SCHUR: return op_schur(c, prec, in[0], *out, tmp[1], RED_NONE, nullptr, nullptr, nullptr, nullptr);
     case LQCD_DPREC_PAPER:
-      // D^(eo) = A_ee^-1 S; S into in_o's buffer (free once the input's odd part is unused)
-      *write_o = false;
-      LQ_TRY(op_schur(c, prec, in_e, in_o, out_o, RED_NONE, nullptr, nullptr, nullptr, nullptr));
-      return launch_site(c, prec, clover_slot(c, prec, 2), in_o, out_e);
+      // D^(eo) = A_ee^-1 S; S into the odd input's buffer (not read)
+      LQ_TRY(op_schur(c, prec, in[0], in[1], tmp[1], RED_NONE, nullptr, nullptr, nullptr, nullptr));
+      return launch_site(c, prec, clover_slot(c, prec, 2), in[1], *out);
+  }
+  *parity = 1;
+  switch (op) {
+    case LQCD_DOO: return launch_site(c, prec, clover_slot(c, prec, 1), in[1], *out);
+    case LQCD_DOO_INV: return launch_site(c, prec, clover_slot(c, prec, 3), in[1], *out);
+    case LQCD_DOE: return op_hop(c, prec, 1, in[0], *out, -k);
+    case LQCD_HOP_OE: return op_hop(c, prec, 1, in[0], *out, 1.0);
   }
   return set_error(LQCD_EINVAL, "unknown operator");
 }
@@ -342,15 +352,19 @@ int lqcd_apply(lqcd_ctx* c, int op, int prec, const double* in, double* out, int
   const double* din = nullptr;
   LQ_TRY(stage_in(c, in, on_device, c->canon_a, bytes, &din));
   double* dout = on_device ? out : reinterpret_cast<double*>(c->canon_b);
-  void *ie = c->half_a[prec], *io = c->half_b[prec], *oe = c->half_c[prec], *oo = c->half_d[prec];
-  LQ_TRY(launch_import_spinor(c, prec, 0, din, ie));
-  LQ_TRY(launch_import_spinor(c, prec, 1, din, io));
-  bool we = true, wo = true;
-  LQ_TRY(apply_halves(c, op, prec, ie, io, oe, oo, &we, &wo));
-  if (we) LQ_TRY(launch_export_spinor(c, prec, 0, oe, dout));
-  else LQ_TRY(launch_zero_parity(c, 0, dout));
-  if (wo) LQ_TRY(launch_export_spinor(c, prec, 1, oo, dout));
-  else LQ_TRY(launch_zero_parity(c, 1, dout));
+  void* const h[2] = {c->half_a[prec], c->half_b[prec]};
+  void* const t[2] = {c->half_c[prec], c->half_d[prec]};
+  const int reads = parities_read(op);
+  if (reads == 3) LQ_TRY(launch_import_both(c, prec, din, h[0], h[1]));
+  else LQ_TRY(launch_import_spinor(c, prec, reads >> 1, din, h[reads >> 1]));
+  if (op == LQCD_D) {
+    LQ_TRY(op_full_canon(c, prec, h[0], h[1], dout));
+  } else {
+    void* res = nullptr;
+    int parity = 0;
+    LQ_TRY(apply_half(c, op, prec, h, t, &res, &parity));
+    LQ_TRY(launch_export_one(c, prec, parity, res, dout));
+  }
   if (!on_device) {
     LQ_HIP(hipMemcpyAsync(out, dout, bytes, hipMemcpyDeviceToHost, c->stream));
     LQ_HIP(hipStreamSynchronize(c->stream));
@@ -382,8 +396,7 @@ int lqcd_solve(lqcd_ctx* c, const double* b, double* x, const lqcd_solve_params*
   const double* db = nullptr;
   LQ_TRY(stage_in(c, b, prm.on_device, c->canon_a, bytes, &db));
   LQ_TRY(check_finite(c, db, full_sites(c) * 24));
-  LQ_TRY(launch_import_spinor(c, 0, 0, db, w->b_e));
-  LQ_TRY(launch_import_spinor(c, 0, 1, db, w->b_o));
+  LQ_TRY(launch_import_both(c, 0, db, w->b_e, w->b_o));
   if (prm.x0) {
     const double* dx0 = nullptr;
     LQ_TRY(stage_in(c, prm.x0, prm.on_device, c->canon_b, bytes, &dx0));
@@ -405,8 +418,7 @@ int lqcd_solve(lqcd_ctx* c, const double* b, double* x, const lqcd_solve_params*
   }
   if (status != LQCD_OK && status != LQCD_ENOCONV && status != LQCD_EBREAKDOWN) return status;
   double* dx = prm.on_device ? x : reinterpret_cast<double*>(c->canon_b);
-  LQ_TRY(launch_export_spinor(c, 0, 0, w->x_e, dx));
-  LQ_TRY(launch_export_spinor(c, 0, 1, w->x_o, dx));
+  LQ_TRY(launch_export_both(c, 0, w->x_e, w->x_o, dx));
   if (!prm.on_device) LQ_HIP(hipMemcpyAsync(x, dx, bytes, hipMemcpyDeviceToHost, c->stream));
   LQ_HIP(hipStreamSynchronize(c->stream));
   if (stats) *stats = st;
@@ -432,11 +444,9 @@ int lqcd_apply_sap(lqcd_ctx* c, const lqcd_sap_params* sp, const double* eta, do
   LQ_TRY(stage_in(c, eta, on_device, c->canon_a, bytes, &din));
   double* dout = on_device ? psi : reinterpret_cast<double*>(c->canon_b);
   void *ie = c->half_a[1], *io = c->half_b[1], *oe = c->half_c[1], *oo = c->half_d[1];
-  LQ_TRY(launch_import_spinor(c, 1, 0, din, ie));
-  LQ_TRY(launch_import_spinor(c, 1, 1, din, io));
+  LQ_TRY(launch_import_both(c, 1, din, ie, io));
   LQ_TRY(sap_apply(c, sp->block, sp->ncycles, sp->nmr, ie, io, oe, oo));
-  LQ_TRY(launch_export_spinor(c, 1, 0, oe, dout));
-  LQ_TRY(launch_export_spinor(c, 1, 1, oo, dout));
+  LQ_TRY(launch_export_both(c, 1, oe, oo, dout));
   if (!on_device) {
     LQ_HIP(hipMemcpyAsync(psi, dout, bytes, hipMemcpyDeviceToHost, c->stream));
     LQ_HIP(hipStreamSynchronize(c->stream));
@@ -459,20 +469,17 @@ int lqcd_solve_sap(lqcd_ctx* c, const double* b, double* x, const lqcd_solve_par
   LQ_TRY(stage_in(c, b, prm.on_device, c->canon_a, bytes, &db));
   LQ_TRY(check_finite(c, db, full_sites(c) * 24));
   void *be = c->half_a[0], *bo = c->half_b[0], *xe = c->half_c[0], *xo = c->half_d[0];
-  LQ_TRY(launch_import_spinor(c, 0, 0, db, be));
-  LQ_TRY(launch_import_spinor(c, 0, 1, db, bo));
+  LQ_TRY(launch_import_both(c, 0, db, be, bo));
   if (prm.x0) {
     const double* dx0 = nullptr;
     LQ_TRY(stage_in(c, prm.x0, prm.on_device, c->canon_b, bytes, &dx0));
-    LQ_TRY(launch_import_spinor(c, 0, 0, dx0, xe));
-    LQ_TRY(launch_import_spinor(c, 0, 1, dx0, xo));
+    LQ_TRY(launch_import_both(c, 0, dx0, xe, xo));
   }
   lqcd_solve_stats st{};
   const int status = solve_sap(c, prm, sp->block, sp->ncycles, sp->nmr, be, bo, xe, xo, prm.x0 == nullptr, st);
   if (status != LQCD_OK && status != LQCD_ENOCONV && status != LQCD_EBREAKDOWN) return status;
   double* dx = prm.on_device ? x : reinterpret_cast<double*>(c->canon_b);
-  LQ_TRY(launch_export_spinor(c, 0, 0, xe, dx));
-  LQ_TRY(launch_export_spinor(c, 0, 1, xo, dx));
+  LQ_TRY(launch_export_both(c, 0, xe, xo, dx));
   if (!prm.on_device) LQ_HIP(hipMemcpyAsync(x, dx, bytes, hipMemcpyDeviceToHost, c->stream));
   LQ_HIP(hipStreamSynchronize(c->stream));
   if (stats) *stats = st;
@@ -795,16 +802,14 @@ static int mg_stage_fine(lqcd_ctx* c, const double* in, int on_device) {
   LQ_TRY(ensure_apply_buffers(c, 1));
   const double* din = nullptr;
   LQ_TRY(stage_in(c, in, on_device, c->canon_a, full_sites(c) * 192, &din));
-  LQ_TRY(launch_import_spinor(c, 1, 0, din, c->half_a[1]));
-  return launch_import_spinor(c, 1, 1, din, c->half_b[1]);
+  return launch_import_both(c, 1, din, c->half_a[1], c->half_b[1]);
 }
 
 // FP32 native halves half_c[1], half_d[1] -> canonical fine field (host or device)
 static int mg_unstage_fine(lqcd_ctx* c, double* out, int on_device) {
   const size_t bytes = full_sites(c) * 192;
   double* dout = on_device ? out : reinterpret_cast<double*>(c->canon_b);
-  LQ_TRY(launch_export_spinor(c, 1, 0, c->half_c[1], dout));
-  LQ_TRY(launch_export_spinor(c, 1, 1, c->half_d[1], dout));
+  LQ_TRY(launch_export_both(c, 1, c->half_c[1], c->half_d[1], dout));
   if (!on_device) LQ_HIP(hipMemcpyAsync(out, dout, bytes, hipMemcpyDeviceToHost, c->stream));
   LQ_HIP(hipStreamSynchronize(c->stream));
   return LQCD_OK;
@@ -892,21 +897,18 @@ int lqcd_solve_mg(lqcd_ctx* c, const double* b, double* x, const lqcd_solve_para
   LQ_TRY(stage_in(c, b, prm.on_device, c->canon_a, bytes, &db));
   LQ_TRY(check_finite(c, db, full_sites(c) * 24));
   void *be = c->half_a[0], *bo = c->half_b[0], *xe = c->half_c[0], *xo = c->half_d[0];
-  LQ_TRY(launch_import_spinor(c, 0, 0, db, be));
-  LQ_TRY(launch_import_spinor(c, 0, 1, db, bo));
+  LQ_TRY(launch_import_both(c, 0, db, be, bo));
   if (prm.x0) {
     const double* dx0 = nullptr;
     LQ_TRY(stage_in(c, prm.x0, prm.on_device, c->canon_b, bytes, &dx0));
-    LQ_TRY(launch_import_spinor(c, 0, 0, dx0, xe));
-    LQ_TRY(launch_import_spinor(c, 0, 1, dx0, xo));
+    LQ_TRY(launch_import_both(c, 0, dx0, xe, xo));
   }
   lqcd_solve_stats st{};
   long coarse = 0;
   const int status = solve_mg(c, prm, be, bo, xe, xo, prm.x0 == nullptr, st, &coarse);
   if (status != LQCD_OK && status != LQCD_ENOCONV && status != LQCD_EBREAKDOWN) return status;
   double* dx = prm.on_device ? x : reinterpret_cast<double*>(c->canon_b);
-  LQ_TRY(launch_export_spinor(c, 0, 0, xe, dx));
-  LQ_TRY(launch_export_spinor(c, 0, 1, xo, dx));
+  LQ_TRY(launch_export_both(c, 0, xe, xo, dx));
   if (!prm.on_device) LQ_HIP(hipMemcpyAsync(x, dx, bytes, hipMemcpyDeviceToHost, c->stream));
   LQ_HIP(hipStreamSynchronize(c->stream));
   if (stats) *stats = st;

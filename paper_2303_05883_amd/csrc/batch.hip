@@ -641,8 +641,7 @@ extern "C" int lqcd_solve_batch(lqcd_ctx* const* ctxs, const int* nrhs, const do
       LQ_HIP(hipMemcpyAsync(c->canon_a, bs, n * sizeof(double), hipMemcpyHostToDevice, stream));
       db = reinterpret_cast<const double*>(c->canon_a);
     }
-    LQ_TRY(launch_import_spinor(c, 0, 0, db, f[0]));
-    LQ_TRY(launch_import_spinor(c, 0, 1, db, f[1]));
+    LQ_TRY(launch_import_both(c, 0, db, f[0], f[1]));
     double* nrm = B.snorm + 16 * s;
     LQ_TRY(seg_norm(c, f[0], nrm + 0));
     LQ_TRY(seg_norm(c, f[1], nrm + 3));
@@ -771,8 +770,7 @@ extern "C" int lqcd_solve_batch(lqcd_ctx* const* ctxs, const int* nrhs, const do
     double* xs = x[l] + (size_t)r * n;
     if (!prm.on_device) LQ_TRY(ensure_canon(c));
     double* dx = prm.on_device ? xs : reinterpret_cast<double*>(c->canon_b);
-    LQ_TRY(launch_export_spinor(c, 0, 0, f[3], dx));
-    LQ_TRY(launch_export_spinor(c, 0, 1, f[4], dx));
+    LQ_TRY(launch_export_both(c, 0, f[3], f[4], dx));
     if (!prm.on_device) {
       LQ_HIP(hipMemcpyAsync(xs, dx, n * sizeof(double), hipMemcpyDeviceToHost, stream));
       LQ_HIP(hipStreamSynchronize(stream));

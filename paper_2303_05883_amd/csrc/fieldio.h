@@ -434,17 +434,16 @@ __device__ inline T quad_sum(T v) {
   return v;
 }
 
-// blockIdx -> logical block: with remap on, each of the 8 XCDs (which receive
-// blocks round-robin) gets one contiguous range of logical blocks, so that
-// neighbouring sites share that XCD's L2.
-__device__ inline int logical_block(int remap) {
-  const int b = blockIdx.x;
+// block b of nb -> logical block: with remap on, each of the 8 XCDs (which
+// receive blocks round-robin) gets one contiguous range of logical blocks, so
+// that neighbouring sites share that XCD's L2.
+__device__ inline int logical_block(int remap, int b, int nb) {
   if (!remap) return b;
-  const int nb = gridDim.x;
   const int q = nb >> 3, r = nb & 7;
   const int xcd = b & 7, idx = b >> 3;
   return xcd * q + (xcd < r ? xcd : r) + idx;
 }
+__device__ inline int logical_block(int remap) { return logical_block(remap, blockIdx.x, gridDim.x); }
 
 // Deterministic block reduction of N doubles: wavefront sums, then the
 // waves' partials summed in wave order by thread 0. Result written to out[0..N).

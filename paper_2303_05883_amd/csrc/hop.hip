@@ -5,7 +5,7 @@
 //
 //   (H psi)(x) = sum_mu eta (1 - gamma_mu) U_mu(x) psi(x+mu) + eta (1 + gamma_mu) U_mu(x-mu)^dag psi(x-mu)
 //
-// One thread per output site. Per direction the neighbour spinor is projected
+// Per direction the neighbour spinor is projected
 // to a half spinor h (2 spins x 3 colours), using (1 -+ gamma_mu) psi =
 // (h, -+ i sigma_mu h) for spatial mu in the Dirac-Pauli basis and
 // (1 -+ gamma_t) = 2 diag(0,0,1,1) / 2 diag(1,1,0,0) in time (so a t hop
@@ -28,17 +28,18 @@
 
 namespace lq {
 
-template <int P, int EPI, bool CLOV, int RED, bool NT>
-__global__ void __launch_bounds__(256) k_hop(HopArgs a) {
-  if (a.skip && *a.skip) return;
-  const int blk = blockIdx.x;
-  size_t i = 0;
-  const bool active = map_site(a, blockDim.x, threadIdx.x, i);
-  constexpr int NR = RED == RED_DOT ? 2 : (RED == RED_TS ? 3 : 0);
-  double red[3] = {0.0, 0.0, 0.0};
-  if (active) hop_site<P, EPI, CLOV, RED, NT>(a, i, red);
-  if constexpr (NR > 0) block_reduce<NR>(red, a.partials + (size_t)blk * NR);
-}
+// The work of block b of nb with SPLIT lanes per output site; this lane's share
+// of the fused reductions into red.
+template <int SPLIT, int P, int EPI, bool CLOV, int RED, bool NT, bool CANON>
+struct HopBody;
+
+template <int P, int EPI, bool CLOV, int RED, bool NT, bool CANON>
+struct HopBody<1, P, EPI, CLOV, RED, NT, CANON> {
+  __device__ static inline void run(const HopArgs& a, int b, int nb, double red[3]) {
+    size_t i = 0;
+    if (map_site(a, b, nb, blockDim.x, threadIdx.x, i)) hop_site<P, EPI, CLOV, RED, NT, CANON>(a, i, red);
+  }
+};
 
 // Direction-split hop: four lanes of a quad share one output site, lane mu
 // taking the forward and backward hops in direction mu. Every lane issues its
@@ -49,17 +50,13 @@ __global__ void __launch_bounds__(256) k_hop(HopArgs a) {
 // of the spin projection and reconstruction, (1 -+ gamma_mu) psi = (h, P h)
 // with h = a u + c0 l_{j0}, ... (see below). The epilogue is computed by all
 // four lanes; the stores are split between them.
-template <int P, int EPI, bool CLOV, int RED, bool NT>
-__global__ void __launch_bounds__(256) k_hop4(HopArgs a) {
-  using T = typename IO<P>::T;
-  if (a.skip && *a.skip) return;
-  const int blk = blockIdx.x;
-  const int mu = threadIdx.x & 3;
-  size_t i = 0;
-  const bool active = map_site(a, blockDim.x >> 2, threadIdx.x >> 2, i);
-  constexpr int NR = RED == RED_DOT ? 2 : (RED == RED_TS ? 3 : 0);
-  double red[3] = {0.0, 0.0, 0.0};
-  if (active) {
+template <int P, int EPI, bool CLOV, int RED, bool NT, bool CANON>
+struct HopBody<4, P, EPI, CLOV, RED, NT, CANON> {
+  __device__ static inline void run(const HopArgs& a, int b, int nblk, double red[3]) {
+    using T = typename IO<P>::T;
+    const int mu = threadIdx.x & 3;
+    size_t i = 0;
+    if (!map_site(a, b, nblk, blockDim.x >> 2, threadIdx.x >> 2, i)) return;
     const Geom& g = a.g;
     const int ii = (int)i;
     const int xh = ii % g.lxh;
@@ -149,10 +146,9 @@ __global__ void __launch_bounds__(256) k_hop4(HopArgs a) {
     cx<T> out[12];
     hop_epilogue<P, EPI, CLOV, RED>(a, i, acc, out, red);
     if (mu != 0) red[0] = red[1] = red[2] = 0.0;
-    IO<P>::store_part(a.out, i, out, mu, 4);
+    hop_store<P, CANON>(a, i, x, out, mu, 4);
   }
-  if constexpr (NR > 0) block_reduce<NR>(red, a.partials + (size_t)blk * NR);
-}
+};
 
 
 // Pair-split hop: two lanes share one output site, one taking the four
@@ -250,19 +246,15 @@ __device__ inline void pair_compute(const PairIn<P>& d, bool fwd, bool flip, cx<
   }
 }
 
-template <int P, int EPI, bool CLOV, int RED, bool NT>
-__global__ void __launch_bounds__(256) k_hop2(HopArgs a) {
-  using T = typename IO<P>::T;
-  if (a.skip && *a.skip) return;
-  const size_t vh = (size_t)a.g.vh;
-  const int blk = blockIdx.x;
-  const int half = (threadIdx.x >> 5) & 1;
-  const bool fwd = half == 0;
-  size_t i = 0;
-  const bool active = map_site(a, blockDim.x >> 1, ((threadIdx.x >> 6) << 5) | (threadIdx.x & 31), i);
-  constexpr int NR = RED == RED_DOT ? 2 : (RED == RED_TS ? 3 : 0);
-  double red[3] = {0.0, 0.0, 0.0};
-  if (active) {
+template <int P, int EPI, bool CLOV, int RED, bool NT, bool CANON>
+struct HopBody<2, P, EPI, CLOV, RED, NT, CANON> {
+  __device__ static inline void run(const HopArgs& a, int b, int nblk, double red[3]) {
+    using T = typename IO<P>::T;
+    const size_t vh = (size_t)a.g.vh;
+    const int half = (threadIdx.x >> 5) & 1;
+    const bool fwd = half == 0;
+    size_t i = 0;
+    if (!map_site(a, b, nblk, blockDim.x >> 1, ((threadIdx.x >> 6) << 5) | (threadIdx.x & 31), i)) return;
     const Geom& g = a.g;
     const int ii = (int)i;
     const int xh = ii % g.lxh;
@@ -312,9 +304,45 @@ __global__ void __launch_bounds__(256) k_hop2(HopArgs a) {
     cx<T> out[12];
     hop_epilogue<P, EPI, CLOV, RED>(a, i, acc, out, red);
     if (half != 0) red[0] = red[1] = red[2] = 0.0;
-    IO<P>::store_part(a.out, i, out, half, 2);
+    hop_store<P, CANON>(a, i, x, out, half, 2);
   }
-  if constexpr (NR > 0) block_reduce<NR>(red, a.partials + (size_t)blk * NR);
+};
+
+template <int SPLIT, int P, int EPI, bool CLOV, int RED, bool NT>
+__global__ void __launch_bounds__(256) k_hop(HopArgs a) {
+  if (a.skip && *a.skip) return;
+  constexpr int NR = RED == RED_DOT ? 2 : (RED == RED_TS ? 3 : 0);
+  double red[3] = {0.0, 0.0, 0.0};
+  HopBody<SPLIT, P, EPI, CLOV, RED, NT, false>::run(a, blockIdx.x, gridDim.x, red);
+  if constexpr (NR > 0) block_reduce<NR>(red, a.partials + (size_t)blockIdx.x * NR);
+}
+
+// The full operator in one launch: 8 blocks (one per XCD) of the even sites, then
+// the 8 of the same ranges of the odd sites, out_p = A_pp x_p + scale H x_{1-p}.
+// Each link is a forward link of one parity and a backward link of the other and
+// each spinor the own site of one and a neighbour of the other, so both are read
+// from memory about once instead of twice, and a small lattice needs one launch.
+// CANON: the result goes straight to the canonical field. lqcd_apply of D with its
+// conversions, against one launch per parity, its own export and an import per
+// parity: FP64 clover 8^4 67 -> 50 us, 24^3x48 435 -> 289, 32^3x64 1242 -> 829; FP32
+// clover 32^3x64 761 -> 555.
+struct HopBoth {
+  const void* x[2];
+  void* out[2];
+  const void* clov[2];
+};
+
+template <int SPLIT, int P, bool CLOV, bool CANON>
+__global__ void __launch_bounds__(256) k_hop_both(HopArgs a, HopBoth w) {
+  const int p = (blockIdx.x >> 3) & 1;
+  a.p = p;
+  a.in = w.x[1 - p];
+  a.xown = w.x[p];
+  a.out = w.out[p];
+  a.clov = w.clov[p];
+  double red[3];
+  HopBody<SPLIT, P, EPI_XPAY, CLOV, RED_NONE, false, CANON>::run(a, (blockIdx.x >> 4) * 8 + (blockIdx.x & 7),
+                                                              gridDim.x >> 1, red);
 }
 
 // ------------------------------------------------------------------ plane march
@@ -610,14 +638,14 @@ static void launch_t(const HopArgs& a, int nb, int bs, hipStream_t s, bool nt, i
     if (ty == a.g.ly) hipLaunchKernelGGL((k_hopz<P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), lds, s, am, ty, a.hz);
     else hipLaunchKernelGGL((k_hopz<P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), lds, s, am, ty, a.hz);
   } else if (split == 4) {
-    if (nt) hipLaunchKernelGGL((k_hop4<P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), 0, s, a);
-    else hipLaunchKernelGGL((k_hop4<P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), 0, s, a);
+    if (nt) hipLaunchKernelGGL((k_hop<4, P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), 0, s, a);
+    else hipLaunchKernelGGL((k_hop<4, P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), 0, s, a);
   } else if (split == 2) {
-    if (nt) hipLaunchKernelGGL((k_hop2<P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), 0, s, a);
-    else hipLaunchKernelGGL((k_hop2<P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), 0, s, a);
+    if (nt) hipLaunchKernelGGL((k_hop<2, P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), 0, s, a);
+    else hipLaunchKernelGGL((k_hop<2, P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), 0, s, a);
   } else {
-    if (nt) hipLaunchKernelGGL((k_hop<P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), 0, s, a);
-    else hipLaunchKernelGGL((k_hop<P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), 0, s, a);
+    if (nt) hipLaunchKernelGGL((k_hop<1, P, EPI, CLOV, RED, true>), dim3(nb), dim3(bs), 0, s, a);
+    else hipLaunchKernelGGL((k_hop<1, P, EPI, CLOV, RED, false>), dim3(nb), dim3(bs), 0, s, a);
   }
 }
 
@@ -665,7 +693,7 @@ int launch_hop(lqcd_ctx* c, const HopCall& h, int* nblocks_out) {
   const int nb = hop_blocks(c, h.prec);
   if (nblocks_out) *nblocks_out = nb;
   if (h.red != RED_NONE && !h.partials) return set_error(LQCD_EINVAL, "reduction without a partials buffer");
-  HopArgs a;
+  HopArgs a{};
   a.in = h.in;
   a.out = h.out;
   a.gauge = reinterpret_cast<const char*>(c->gauge[h.prec]);
@@ -691,6 +719,55 @@ int launch_hop(lqcd_ctx* c, const HopCall& h, int* nblocks_out) {
     case 2: return dispatch<2>(c, h, a, nb, bs);
   }
   return set_error(LQCD_EINVAL, "bad precision");
+}
+
+// The shape of k_hop_both, which holds twice a hop's sites and wants its links in
+// the caches (they are read again by the other parity): four or two lanes per
+// site while the launch does not fill the chip, else one, in XCD z slabs where
+// they fit. lqcd_apply of D, clover, us: 16^3x32 FP64 two lanes 69, one 75; 30x22x26x38
+// FP64 313 and 297, FP32 214 and 199; 32^3x64 FP64 workgroups of 64 in slabs 828, of
+// 256 838, in site order 888, links streamed 873.
+template <int P, bool CLOV, bool CANON>
+static void launch_both_t(HopArgs& a, const HopBoth& w, hipStream_t s) {
+  const int vh = a.g.vh;
+  const int split = vh <= 12000 ? 4 : (vh <= 100000 ? 2 : 1);
+  const int bs = split == 1 && P != 0 ? 256 : 64;
+  a.remap = split == 1 && a.g.lz % 8 == 0 ? 2 : 1;
+  a.hz = a.g.lz / 8;
+  const int sites = bs / split, range = a.remap == 2 ? vh / 8 : (vh + 7) / 8;
+  const dim3 g(16 * ((range + sites - 1) / sites)), b(bs);  // whole rounds of the 8 XCDs per parity
+  if (split == 4) hipLaunchKernelGGL((k_hop_both<4, P, CLOV, CANON>), g, b, 0, s, a, w);
+  else if (split == 2) hipLaunchKernelGGL((k_hop_both<2, P, CLOV, CANON>), g, b, 0, s, a, w);
+  else hipLaunchKernelGGL((k_hop_both<1, P, CLOV, CANON>), g, b, 0, s, a, w);
+}
+
+template <int P>
+static void launch_both_p(HopArgs& a, const HopBoth& w, hipStream_t s) {
+  if (a.canon) {
+    if (w.clov[0]) launch_both_t<P, true, true>(a, w, s);
+    else launch_both_t<P, false, true>(a, w, s);
+  } else {
+    if (w.clov[0]) launch_both_t<P, true, false>(a, w, s);
+    else launch_both_t<P, false, false>(a, w, s);
+  }
+}
+
+int launch_hop_both(lqcd_ctx* c, int prec, const void* const x[2], const void* const clov[2], double scale,
+                    void* const out[2], double* canon) {
+  if (prec < 0 || prec > 2) return set_error(LQCD_EINVAL, "bad precision");
+  if (!c->gauge[prec]) return set_error(LQCD_ESTATE, "gauge field not set");
+  HopArgs a{};
+  a.gauge = reinterpret_cast<const char*>(c->gauge[prec]);
+  a.link_stride = link_bytes(prec, c->g.vh);
+  a.g = c->g;
+  a.scale = scale;
+  a.canon = canon;
+  const HopBoth w{{x[0], x[1]}, {out ? out[0] : nullptr, out ? out[1] : nullptr}, {clov[0], clov[1]}};
+  if (prec == 0) launch_both_p<0>(a, w, c->stream);
+  else if (prec == 1) launch_both_p<1>(a, w, c->stream);
+  else launch_both_p<2>(a, w, c->stream);
+  LQ_HIP(hipGetLastError());
+  return LQCD_OK;
 }
 
 int launch_site(lqcd_ctx* c, int prec, const void* clov, const void* in, void* out) {

@@ -211,16 +211,17 @@ struct HopArgs {
   int p;
   int remap;  // 0: linear, 1: XCD-contiguous ranges, 2: XCD z-slabs (see map_site)
   int hz;     // z extent of one XCD slab (remap 2)
+  double* canon;  // where the result goes as a canonical field (hop_store with CANON)
 };
 
-// Site of this thread (local = index among the block's sites, spb sites per
-// block). remap 2 gives XCD k (blocks are dealt to the 8 XCDs round-robin) the
+// Site of this thread of block b of nb (local = index among the block's sites,
+// spb sites per block). remap 2 gives XCD k (blocks are dealt to the 8 XCDs round-robin) the
 // slab z in [k hz, (k+1) hz) and walks it x, y fastest, then z, then t, so that
 // the z and t neighbours of the sites in flight were read shortly before and
 // are still in that XCD's L2. Returns false for threads past the slab's end.
-__device__ inline bool map_site(const HopArgs& a, int spb, int local, size_t& i) {
+__device__ inline bool map_site(const HopArgs& a, int b, int nb, int spb, int local, size_t& i) {
   if (a.remap == 2) {
-    const int k = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int k = b & 7, j = b >> 3;
     const int xy = a.g.lxh * a.g.ly;
     const int q = j * spb + local;
     if (q >= xy * a.hz * a.g.lt) return false;
@@ -229,7 +230,7 @@ __device__ inline bool map_site(const HopArgs& a, int spb, int local, size_t& i)
     i = (size_t)xyi + (size_t)xy * ((size_t)(k * a.hz + zin) + (size_t)a.g.lz * t);
     return true;
   }
-  i = (size_t)logical_block(a.remap) * spb + local;
+  i = (size_t)logical_block(a.remap, b, nb) * spb + local;
   return i < (size_t)a.g.vh;
 }
 
@@ -284,9 +285,38 @@ __device__ inline void hop_epilogue(const HopArgs& a, size_t i, cx<typename IO<P
 }
 
 
+// The words k with k % nl == lane of the result at site i (x: its x coordinate),
+// stored in the native layout, or with CANON as complex128 at the site's place in
+// the canonical field (site 2 i + (x & 1) of the full lattice).
+template <int P, bool CANON>
+__device__ inline void hop_store(const HopArgs& a, size_t i, int x, const cx<typename IO<P>::T> out[12], int lane,
+                                 int nl) {
+  if constexpr (CANON) {
+    double2* dst = reinterpret_cast<double2*>(a.canon) + 12 * (2 * i + (x & 1));
+    cx<typename IO<P>::T> v[12];
+    if (P == 2) {  // the FP16 layout rounds: store what it would hold
+      float m = 0.f;
+#pragma unroll
+      for (int k = 0; k < 12; ++k) m = fmaxf(m, fmaxf(fabsf((float)out[k].r), fabsf((float)out[k].i)));
+      const float inv = m > 0.f ? 1.0f / m : 0.f;
+#pragma unroll
+      for (int k = 0; k < 12; ++k)
+        v[k] = {m * (float)(_Float16)((float)out[k].r * inv), m * (float)(_Float16)((float)out[k].i * inv)};
+    } else {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) v[k] = out[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+      if (k % nl == lane) dst[k] = make_double2((double)v[k].r, (double)v[k].i);
+  } else {
+    IO<P>::store_part(a.out, i, out, lane, nl);
+  }
+}
+
 // One output site of the 1-lane hop: H psi at site i, the epilogue, the store,
 // and this site's share of the fused reductions added into red.
-template <int P, int EPI, bool CLOV, int RED, bool NT>
+template <int P, int EPI, bool CLOV, int RED, bool NT, bool CANON = false>
 __device__ inline void hop_site(const HopArgs& a, size_t i, double red[3]) {
   using T = typename IO<P>::T;
   const size_t vh = (size_t)a.g.vh;
@@ -331,7 +361,7 @@ __device__ inline void hop_site(const HopArgs& a, size_t i, double red[3]) {
 
   cx<T> out[12];
   hop_epilogue<P, EPI, CLOV, RED>(a, i, acc, out, red);
-  IO<P>::store_spinor(a.out, i, out);
+  hop_store<P, CANON>(a, i, x, out, 0, 1);
 }
 
 // ------------------------------------------------------------------ several right-hand sides

@@ -180,7 +180,10 @@ int ensure_canon(lqcd_ctx* c);
 // layout.hip
 int launch_import_spinor(lqcd_ctx* c, int prec, int parity, const double* canon, void* half);
 int launch_export_spinor(lqcd_ctx* c, int prec, int parity, const void* half, double* canon);
-int launch_zero_parity(lqcd_ctx* c, int parity, double* canon);
+// both parities at once; launch_export_one sets the sites of the other parity to zero
+int launch_import_both(lqcd_ctx* c, int prec, const double* canon, void* even, void* odd);
+int launch_export_both(lqcd_ctx* c, int prec, const void* even, const void* odd, double* canon);
+int launch_export_one(lqcd_ctx* c, int prec, int parity, const void* half, double* canon);
 int launch_import_gauge(lqcd_ctx* c, const double* canon, double* check /* device, 3 doubles */);
 int launch_convert_field(lqcd_ctx* c, int src_prec, const void* src, int dst_prec, void* dst);
 int launch_check_finite(lqcd_ctx* c, const double* p, size_t n, double* flag);
@@ -206,6 +209,10 @@ struct HopCall {
   const int* skip;      // optional device flag: when nonzero the launch does nothing
 };
 int launch_hop(lqcd_ctx* c, const HopCall& h, int* nblocks_out);
+// out_p = clov_p x_p + scale H x_{1-p} for both parities p in one launch (clov null:
+// 1), as half fields out or, with canon, as one canonical field.
+int launch_hop_both(lqcd_ctx* c, int prec, const void* const x[2], const void* const clov[2], double scale,
+                    void* const out[2], double* canon);
 // Progress lines on stderr when LQCD_LOG is set (each outer pass, and every
 // inner convergence check when LQCD_LOG=2).
 inline int log_level() {

@@ -55,14 +55,46 @@ __global__ void __launch_bounds__(256) k_export_spinor(Geom g, int p, const void
   for (int k = 0; k < 12; ++k) dst[k] = make_double2((double)s[k].r, (double)s[k].i);
 }
 
-__global__ void __launch_bounds__(256) k_zero_parity(Geom g, int p, double* canon) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.vh) return;
-  int x, y, z, t;
-  site_coords(g, p, i, x, y, z, t);
-  double2* dst = reinterpret_cast<double2*>(canon) + 12 * full_index(g, x, y, z, t);
+// Both parities in one launch, one lane per site of the full lattice in canonical
+// order: site f is checkerboard site f / 2 of its parity. The wavefront reads or
+// writes the 12 KiB of its 64 sites of the canonical field in one run.
+__device__ inline int parity_of(const Geom& g, size_t f) {
+  const int x = (int)(f % g.lx);
+  size_t r = f / g.lx;
+  const int y = (int)(r % g.ly);
+  r /= g.ly;
+  return (x + y + (int)(r % g.lz) + (int)(r / g.lz)) & 1;
+}
+
+template <int P>
+__global__ void __launch_bounds__(256) k_import_both(Geom g, const double* canon, void* even, void* odd) {
+  using T = typename IO<P>::T;
+  const size_t f = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (f >= 2 * (size_t)g.vh) return;
+  const double2* src = reinterpret_cast<const double2*>(canon) + 12 * f;
+  cx<T> s[12];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) dst[k] = make_double2(0.0, 0.0);
+  for (int k = 0; k < 12; ++k) {
+    const double2 v = src[k];
+    s[k] = {(T)v.x, (T)v.y};
+  }
+  IO<P>::store_spinor(parity_of(g, f) ? odd : even, f >> 1, s);
+}
+
+// even or odd may be null: zero there
+template <int P>
+__global__ void __launch_bounds__(256) k_export_both(Geom g, const void* even, const void* odd, double* canon) {
+  using T = typename IO<P>::T;
+  const size_t f = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (f >= 2 * (size_t)g.vh) return;
+  const void* half = parity_of(g, f) ? odd : even;
+  double2* dst = reinterpret_cast<double2*>(canon) + 12 * f;
+  cx<T> s[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) s[k] = {T(0), T(0)};
+  if (half) IO<P>::load_spinor(half, f >> 1, s);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) dst[k] = make_double2((double)s[k].r, (double)s[k].i);
 }
 
 // Atomic max of a non-negative double kept as its bit pattern (monotone for
@@ -187,10 +219,32 @@ int launch_export_spinor(lqcd_ctx* c, int prec, int parity, const void* half, do
   return LQCD_OK;
 }
 
-int launch_zero_parity(lqcd_ctx* c, int parity, double* canon) {
-  hipLaunchKernelGGL(k_zero_parity, dim3(grid_for(c->g.vh, 256)), dim3(256), 0, c->stream, c->g, parity, canon);
+int launch_import_both(lqcd_ctx* c, int prec, const double* canon, void* even, void* odd) {
+  const dim3 nb(grid_for(2 * (size_t)c->g.vh, 256)), b(256);
+  switch (prec) {
+    case 0: hipLaunchKernelGGL(k_import_both<0>, nb, b, 0, c->stream, c->g, canon, even, odd); break;
+    case 1: hipLaunchKernelGGL(k_import_both<1>, nb, b, 0, c->stream, c->g, canon, even, odd); break;
+    case 2: hipLaunchKernelGGL(k_import_both<2>, nb, b, 0, c->stream, c->g, canon, even, odd); break;
+    default: return set_error(LQCD_EINVAL, "bad precision");
+  }
   LQ_HIP(hipGetLastError());
   return LQCD_OK;
+}
+
+int launch_export_both(lqcd_ctx* c, int prec, const void* even, const void* odd, double* canon) {
+  const dim3 nb(grid_for(2 * (size_t)c->g.vh, 256)), b(256);
+  switch (prec) {
+    case 0: hipLaunchKernelGGL(k_export_both<0>, nb, b, 0, c->stream, c->g, even, odd, canon); break;
+    case 1: hipLaunchKernelGGL(k_export_both<1>, nb, b, 0, c->stream, c->g, even, odd, canon); break;
+    case 2: hipLaunchKernelGGL(k_export_both<2>, nb, b, 0, c->stream, c->g, even, odd, canon); break;
+    default: return set_error(LQCD_EINVAL, "bad precision");
+  }
+  LQ_HIP(hipGetLastError());
+  return LQCD_OK;
+}
+
+int launch_export_one(lqcd_ctx* c, int prec, int parity, const void* half, double* canon) {
+  return launch_export_both(c, prec, parity == 0 ? half : nullptr, parity == 0 ? nullptr : half, canon);
 }
 
 int launch_import_gauge(lqcd_ctx* c, const double* canon, double* check) {

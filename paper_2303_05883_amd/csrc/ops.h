@@ -17,6 +17,8 @@ int op_schur(lqcd_ctx* c, int prec, const void* in, void* out, void* tmp_odd, in
              double* partials, const int* skip, int* nblocks);
 // full D on a pair of half fields
 int op_full(lqcd_ctx* c, int prec, const void* in_e, const void* in_o, void* out_e, void* out_o);
+// the same with the result as a canonical field
+int op_full_canon(lqcd_ctx* c, int prec, const void* in_e, const void* in_o, double* canon);
 // one native operator (see lqcd_apply_native)
 int op_native(lqcd_ctx* c, int op, int prec, const void* in, void* out, void* tmp_odd);
 

@@ -72,9 +72,16 @@ int op_schur(lqcd_ctx* c, int prec, const void* in, void* out, void* tmp_odd, in
 }
 
 int op_full(lqcd_ctx* c, int prec, const void* in_e, const void* in_o, void* out_e, void* out_o) {
-  const double k = c->kappa;
-  LQ_TRY(op_hop_xpay(c, prec, 0, in_o, in_e, clover_slot(c, prec, 0), out_e, -k));
-  return op_hop_xpay(c, prec, 1, in_e, in_o, clover_slot(c, prec, 1), out_o, -k);
+  const void* const x[2] = {in_e, in_o};
+  void* const out[2] = {out_e, out_o};
+  const void* const clov[2] = {clover_slot(c, prec, 0), clover_slot(c, prec, 1)};
+  return launch_hop_both(c, prec, x, clov, -c->kappa, out, nullptr);
+}
+
+int op_full_canon(lqcd_ctx* c, int prec, const void* in_e, const void* in_o, double* canon) {
+  const void* const x[2] = {in_e, in_o};
+  const void* const clov[2] = {clover_slot(c, prec, 0), clover_slot(c, prec, 1)};
+  return launch_hop_both(c, prec, x, clov, -c->kappa, nullptr, canon);
 }
 
 int op_native(lqcd_ctx* c, int op, int prec, const void* in, void* out, void* tmp_odd) {
