@@ -327,12 +327,43 @@ struct IO<2> {
   }
 };
 
+// Fused multiply-add forms of the complex arithmetic: four FMAs per complex
+// multiply-accumulate where a product and a sum take six instructions. Hops are
+// bounded by memory at large sizes, so a fifth fewer instructions give little
+// there; in the clover term (Schur operator, us, before and after): FP64 24^3x48
+// 250 and 235, FP16 24^3x48 62.1 and 59.5, 32^3x64 185 and 181.
+__device__ inline float fmat(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ inline double fmat(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// c + a b and c + conj(a) b
+template <typename T>
+__device__ inline cx<T> cmadd(cx<T> a, cx<T> b, cx<T> c) {
+  return {fmat(-a.i, b.i, fmat(a.r, b.r, c.r)), fmat(a.i, b.r, fmat(a.r, b.i, c.i))};
+}
+template <typename T>
+__device__ inline cx<T> cmaddc(cx<T> a, cx<T> b, cx<T> c) {
+  return {fmat(a.i, b.i, fmat(a.r, b.r, c.r)), fmat(-a.i, b.r, fmat(a.r, b.i, c.i))};
+}
+// c + f z, c + f (i z), c - f (i z) for a real factor f
+template <typename T>
+__device__ inline cx<T> caxpy(T f, cx<T> z, cx<T> c) {
+  return {fmat(f, z.r, c.r), fmat(f, z.i, c.i)};
+}
+template <typename T>
+__device__ inline cx<T> caxpy_i(T f, cx<T> z, cx<T> c) {
+  return {fmat(-f, z.i, c.r), fmat(f, z.r, c.i)};
+}
+template <typename T>
+__device__ inline cx<T> caxpy_mi(T f, cx<T> z, cx<T> c) {
+  return {fmat(f, z.i, c.r), fmat(-f, z.r, c.i)};
+}
+
 // Rebuild row 2 of an SU(3) matrix from rows 0, 1: row2 = conj(row0 x row1).
 template <typename T>
 __device__ inline void reconstruct(const cx<T> u[6], cx<T> r2[3]) {
-  r2[0] = conj(u[1] * u[5] - u[2] * u[4]);
-  r2[1] = conj(u[2] * u[3] - u[0] * u[5]);
-  r2[2] = conj(u[0] * u[4] - u[1] * u[3]);
+  r2[0] = conj(cmadd(-u[2], u[4], u[1] * u[5]));
+  r2[1] = conj(cmadd(-u[0], u[5], u[2] * u[3]));
+  r2[2] = conj(cmadd(-u[1], u[3], u[0] * u[4]));
 }
 
 // y = M x for a Hermitian 6x6 block in the 18-slot packed form.
@@ -347,8 +378,8 @@ __device__ inline void herm6_mul(const cx<T> m[18], const cx<T> x[6], cx<T> y[6]
 #pragma unroll
     for (int b = a + 1; b < 6; ++b) {
       const cx<T> c = m[k++];
-      y[a] = y[a] + c * x[b];
-      y[b] = y[b] + cmulc(c, x[a]);
+      y[a] = cmadd(c, x[b], y[a]);
+      y[b] = cmaddc(c, x[a], y[b]);
     }
   }
 }

@@ -8,35 +8,6 @@
 
 namespace lq {
 
-// Fused multiply-add forms of the complex arithmetic (four FMAs per complex
-// multiply-accumulate), used where the hop is bounded by vector issue: the
-// multi-RHS hop and the FP16 hop (conversions on top of the arithmetic).
-__device__ inline float fmat(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ inline double fmat(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// c + a b and c + conj(a) b
-template <typename T>
-__device__ inline cx<T> cmadd(cx<T> a, cx<T> b, cx<T> c) {
-  return {fmat(-a.i, b.i, fmat(a.r, b.r, c.r)), fmat(a.i, b.r, fmat(a.r, b.i, c.i))};
-}
-template <typename T>
-__device__ inline cx<T> cmaddc(cx<T> a, cx<T> b, cx<T> c) {
-  return {fmat(a.i, b.i, fmat(a.r, b.r, c.r)), fmat(-a.i, b.r, fmat(a.r, b.i, c.i))};
-}
-// c + f z, c + f (i z), c - f (i z) for a real factor f
-template <typename T>
-__device__ inline cx<T> caxpy(T f, cx<T> z, cx<T> c) {
-  return {fmat(f, z.r, c.r), fmat(f, z.i, c.i)};
-}
-template <typename T>
-__device__ inline cx<T> caxpy_i(T f, cx<T> z, cx<T> c) {
-  return {fmat(-f, z.i, c.r), fmat(f, z.r, c.i)};
-}
-template <typename T>
-__device__ inline cx<T> caxpy_mi(T f, cx<T> z, cx<T> c) {
-  return {fmat(f, z.i, c.r), fmat(-f, z.r, c.i)};
-}
-
 // acc += f * (the four-spinor of w = U h for direction MU), f real: the
 // projection's factor (2 and the boundary sign in t) and the FP16 scale.
 template <int MU, bool FWD, typename T>
@@ -69,26 +40,8 @@ __device__ inline void expand_f(cx<T> acc[12], const cx<T> w[6], T f) {
   }
 }
 
-// y = M x (M Hermitian 6x6 in the 18-slot packed form), fused multiply-adds.
-template <typename T>
-__device__ inline void herm6_mul_fma(const cx<T> m[18], const cx<T> x[6], cx<T> y[6]) {
-  const T d[6] = {m[0].r, m[0].i, m[1].r, m[1].i, m[2].r, m[2].i};
-#pragma unroll
-  for (int a = 0; a < 6; ++a) y[a] = d[a] * x[a];
-  int k = 3;
-#pragma unroll
-  for (int a = 0; a < 6; ++a) {
-#pragma unroll
-    for (int b = a + 1; b < 6; ++b) {
-      const cx<T> c = m[k++];
-      y[a] = cmadd(c, x[b], y[a]);
-      y[b] = cmaddc(c, x[a], y[b]);
-    }
-  }
-}
-
-// Spin projection for direction MU; FWD: (1 - gamma_mu), else (1 + gamma_mu).
-// s: 12 complex (3*spin + colour), or for MU == 3 only the 6 needed (see below).
+// Spin projection for direction MU (x, y or z); FWD: (1 - gamma_mu), else (1 +
+// gamma_mu).
 template <int MU, bool FWD, typename T>
 __device__ inline void project(const cx<T> s[12], cx<T> h[6]) {
 #pragma unroll
@@ -107,60 +60,31 @@ __device__ inline void project(const cx<T> s[12], cx<T> h[6]) {
   }
 }
 
-// Accumulate the expanded spinor of w = U h (two colour vectors w[0..2], w[3..5]).
-template <int MU, bool FWD, typename T>
-__device__ inline void expand(cx<T> acc[12], const cx<T> w[6]) {
+// w = M h (FWD) or M^dag h, for both colour vectors of h. FUSED: four multiply-adds
+// per complex product and sum instead of six instructions.
+template <bool FWD, bool FUSED = true, typename T>
+__device__ inline void mat3_mul(const cx<T> M[9], const cx<T> h[6], cx<T> w[6]) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const cx<T> w0 = w[c], w1 = w[3 + c];
-    if (MU == 3) {
-      if (FWD) {  // (1 - gamma_t): lower spins
-        acc[6 + c] = acc[6 + c] + w0;
-        acc[9 + c] = acc[9 + c] + w1;
-      } else {
-        acc[c] = acc[c] + w0;
-        acc[3 + c] = acc[3 + c] + w1;
+  for (int v = 0; v < 2; ++v)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      cx<T> q = FWD ? M[3 * a] * h[3 * v] : cmulc(M[a], h[3 * v]);
+#pragma unroll
+      for (int b = 1; b < 3; ++b) {
+        const cx<T> hb = h[3 * v + b];
+        if (FUSED) q = FWD ? cmadd(M[3 * a + b], hb, q) : cmaddc(M[3 * b + a], hb, q);
+        else q = q + (FWD ? M[3 * a + b] * hb : cmulc(M[3 * b + a], hb));
       }
-      continue;
+      w[3 * v + a] = q;
     }
-    acc[c] = acc[c] + w0;
-    acc[3 + c] = acc[3 + c] + w1;
-    if (MU == 0) {  // lower = -+ i sigma_x w = -+ i (w1, w0)
-      acc[6 + c] = acc[6 + c] + (FWD ? mul_mi(w1) : mul_i(w1));
-      acc[9 + c] = acc[9 + c] + (FWD ? mul_mi(w0) : mul_i(w0));
-    } else if (MU == 1) {  // -+ i sigma_y w = -+ (w1, -w0)
-      acc[6 + c] = FWD ? acc[6 + c] - w1 : acc[6 + c] + w1;
-      acc[9 + c] = FWD ? acc[9 + c] + w0 : acc[9 + c] - w0;
-    } else {  // -+ i sigma_z w = -+ (i w0, -i w1)
-      acc[6 + c] = acc[6 + c] + (FWD ? mul_mi(w0) : mul_i(w0));
-      acc[9 + c] = acc[9 + c] + (FWD ? mul_i(w1) : mul_mi(w1));
-    }
-  }
 }
-
-// w = U h (FWD) or U^dag h, for both colour vectors of h.
-template <bool FWD, typename T>
+// The same with U given by its first two rows.
+template <bool FWD, bool FUSED = true, typename T>
 __device__ inline void link_mul(const cx<T> u[6], const cx<T> h[6], cx<T> w[6]) {
   cx<T> r2[3];
   reconstruct(u, r2);
-  const cx<T> m[9] = {u[0], u[1], u[2], u[3], u[4], u[5], r2[0], r2[1], r2[2]};
-#pragma unroll
-  for (int v = 0; v < 2; ++v) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      cx<T> s;
-      if (FWD) {
-        s = m[3 * a] * h[3 * v];
-        s = s + m[3 * a + 1] * h[3 * v + 1];
-        s = s + m[3 * a + 2] * h[3 * v + 2];
-      } else {
-        s = cmulc(m[a], h[3 * v]);
-        s = s + cmulc(m[3 + a], h[3 * v + 1]);
-        s = s + cmulc(m[6 + a], h[3 * v + 2]);
-      }
-      w[3 * v + a] = s;
-    }
-  }
+  const cx<T> M[9] = {u[0], u[1], u[2], u[3], u[4], u[5], r2[0], r2[1], r2[2]};
+  mat3_mul<FWD, FUSED>(M, h, w);
 }
 
 // G5: the hop acts on gamma5 psi instead of psi (gamma5 of the Dirac-Pauli
@@ -170,13 +94,11 @@ __device__ inline void hop_dir(const void* in, const void* links, size_t vh, siz
                                cx<typename IO<P>::T> acc[12]) {
   using T = typename IO<P>::T;
   cx<T> h[6];
+  T f = 1;  // the factor of the projection in t, applied to w
   if (MU == 3) {
     // (1 - gamma_t) psi = 2 (0, 0, psi_2, psi_3); (1 + gamma_t) psi = 2 (psi_0, psi_1, 0, 0)
-    cx<T> half[6];
-    IO<P>::load_half(in, nbr, G5 ? FWD : !FWD, half);
-    const T two = (flip != G5) ? T(-2) : T(2);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) h[k] = two * half[k];
+    IO<P>::load_half(in, nbr, G5 ? FWD : !FWD, h);
+    f = (flip != G5) ? T(-2) : T(2);
   } else {
     cx<T> s[12];
     IO<P>::load_spinor(in, nbr, s);
@@ -192,8 +114,11 @@ __device__ inline void hop_dir(const void* in, const void* links, size_t vh, siz
   }
   cx<T> u[6], w[6];
   IO<P>::template load_link<NT>(links, lidx, u);
-  link_mul<FWD>(u, h, w);
-  expand<MU, FWD>(acc, w);
+  // FP16 one lane per site: with the fused product the compiler keeps 150-180
+  // VGPRs instead of 93 and the occupancy falls from 5 to 2-3 waves per SIMD
+  // (32^3x64, Schur with clover: 194 against 183 us).
+  link_mul<FWD, P != 2>(u, h, w);
+  expand_f<MU, FWD>(acc, w, f);
 }
 
 struct HopArgs {
@@ -368,10 +293,9 @@ __device__ inline void hop_site(const HopArgs& a, size_t i, double red[3]) {
 // NB right-hand sides of one lattice at one site: each link (and its rebuilt
 // third row) is loaded once per direction and applied to every right-hand
 // side, so the link traffic per site-RHS falls by NB. act has bit r set for
-// the right-hand sides to compute (uniform over a wavefront). The arithmetic is
-// written as fused multiply-adds (four per complex multiply-accumulate): with
-// the links shared, the multiply-RHS hop is bounded by vector issue as much as
-// by memory.
+// the right-hand sides to compute (uniform over a wavefront). With the
+// links shared, the multiple-RHS hop is bounded by vector issue as much as by
+// memory.
 template <int NB>
 struct MultiPtrs {
   const void* in[NB];
@@ -404,22 +328,7 @@ __device__ inline void hop_dir_multi(const MultiPtrs<NB>& m, const void* links, 
       project<MU, FWD>(s, h);
     }
     cx<T> w[6];
-#pragma unroll
-    for (int v = 0; v < 2; ++v)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        cx<T> q;
-        if (FWD) {
-          q = M[3 * a] * h[3 * v];
-          q = cmadd(M[3 * a + 1], h[3 * v + 1], q);
-          q = cmadd(M[3 * a + 2], h[3 * v + 2], q);
-        } else {
-          q = cmulc(M[a], h[3 * v]);
-          q = cmaddc(M[3 + a], h[3 * v + 1], q);
-          q = cmaddc(M[6 + a], h[3 * v + 2], q);
-        }
-        w[3 * v + a] = q;
-      }
+    mat3_mul<FWD>(M, h, w);
     expand_f<MU, FWD>(acc[r], w, f);
   }
 }
@@ -487,7 +396,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6];
-      herm6_mul_fma(mb, acc[q], yv);
+      herm6_mul(mb, acc[q], yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) acc[q][k] = yv[k];
     }
@@ -496,7 +405,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6], out[12];
-      herm6_mul_fma(mb, acc[q] + 6, yv);
+      herm6_mul(mb, acc[q] + 6, yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
         out[k] = acc[q][k] + yv[k];
@@ -528,7 +437,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6];
-      herm6_mul_fma(mb, xo[q], yv);
+      herm6_mul(mb, xo[q], yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) xo[q][k] = yv[k];
     }
@@ -537,7 +446,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6], out[12];
-      herm6_mul_fma(mb, xo[q] + 6, yv);
+      herm6_mul(mb, xo[q] + 6, yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
         out[k] = caxpy(sc, acc[q][k], xo[q][k] + yv[k]);

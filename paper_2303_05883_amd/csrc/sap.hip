@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(512) k_sap_block(SapArgs a) {
       words_get(Lr + 3 * (1 - h) * n, n, l, o);
 #pragma unroll
       for (int k = 0; k < 6; ++k) ch[k] = fwd ? r[k] - o[k] : o[k] + r[k];
-      herm6_mul_fma(cb, ch, yv);
+      herm6_mul(cb, ch, yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
         qv[k] = qv[k] + yv[k];
