@@ -378,9 +378,10 @@ __global__ void __launch_bounds__(256) k_mg_prolong(MgGeom m, const char* B, con
 // (D_c x)_q for row q, added over the SUB lanes of the row (every lane of them
 // gets it): the 9 n pairs of columns of the row's stencil blocks are dealt to
 // the lanes in turn. The rows of a block sit side by side for each pair of
-// columns, so the lanes of consecutive rows read consecutive 16 bytes.
-template <int SUB>
-__device__ inline float2 coarse_row(const MgGeom& m, const float2* M, const float2* x, size_t q, int sub) {
+// columns, so the lanes of consecutive rows read consecutive 16 bytes. x(k) is
+// the k-th pair of the vector's elements.
+template <int SUB, typename X>
+__device__ inline float2 coarse_row(const MgGeom& m, const float2* M, X x, size_t q, int sub) {
   const int n2 = 2 * m.n;
   float re = 0.f, im = 0.f;
   if (q < (size_t)m.nagg * n2) {
@@ -404,9 +405,9 @@ __device__ inline float2 coarse_row(const MgGeom& m, const float2* M, const floa
         nb = cc[0] + m.na[0] * (cc[1] + m.na[1] * (cc[2] + m.na[2] * cc[3]));
       }
       const float4* Mr = reinterpret_cast<const float4*>(M + ((size_t)agg * 9 + dir) * n2 * n2) + row;
-      const float4* xv = reinterpret_cast<const float4*>(x + (size_t)nb * n2);
+      const size_t xv = (size_t)nb * m.n;
       for (int c = sub % CS; c < n2 / 2; c += CS) {
-        const float4 a = Mr[(size_t)c * n2], b = xv[c];
+        const float4 a = Mr[(size_t)c * n2], b = x(xv + c);
         re += a.x * b.x - a.y * b.y + a.z * b.z - a.w * b.w;
         im += a.x * b.y + a.y * b.x + a.z * b.w + a.w * b.z;
       }
@@ -422,8 +423,7 @@ __device__ inline float2 coarse_row(const MgGeom& m, const float2* M, const floa
 
 // The scalars of one coarse BiCGStab, on the device. The kernels of an
 // iteration add the partial sums they need themselves, each workgroup for
-// itself and all in the same order, so an iteration is five launches and no
-// host round trip; workgroup 0 writes what later launches read. done may be set
+// itself and all in the same order, so an iteration has no host round trip; workgroup 0 writes what later launches read. done may be set
 // while other workgroups of the same launch look at it: what they would still
 // write is not read any more.
 struct CoarseState {
@@ -443,15 +443,14 @@ __device__ inline void cs_stop(CoarseState* st, int iters) {
 __device__ inline float2 fmulc(float2 s, float2 v) { return make_float2(s.x * v.x - s.y * v.y, s.x * v.y + s.y * v.x); }
 __device__ inline float2 fadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 
-// y = D_c x. DOT 1: partial sums of <w, y>; DOT 2: of <x, y> and <y, y> (FP64, one
-// record per workgroup). Bound by the latency of its loads on small coarse
-// lattices: 512 aggregates of 16 rows 9.0 us with 4 lanes per row and no dot
-// product, 6.6 us with 16 lanes and the dot product; from 131072 rows on
-// (32^3x64, 4^4 aggregates) by the operator's own bytes, and 4 lanes are kept.
-template <int SUB, int DOT>
-__global__ void __launch_bounds__(256) k_mg_capply(MgGeom m, const float2* M, const float2* x, float2* y,
-                                                   const float2* w, double* partials, const CoarseState* st) {
-  if (DOT && cs_done(st)) return;
+// y = D_c x at this lane's row, x(k) as in coarse_row; the row's lane 0 stores it.
+// DOT 1: partial sums of <w, y>; DOT 2: of <x_q, y> and <y, y> (FP64, one record
+// per workgroup). Bound by the latency of its loads on small coarse lattices: 512
+// aggregates of 16 rows 9.0 us with 4 lanes per row and no dot product, 6.6 us
+// with 16 lanes and the dot product; from 131072 rows on (32^3x64, 4^4
+// aggregates) by the operator's own bytes, and 4 lanes are kept.
+template <int SUB, int DOT, typename X>
+__device__ inline void capply_body(const MgGeom& m, const float2* M, X x, float2* y, const float2* w, double* partials) {
   const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t q = t / SUB;
   const int sub = (int)(t % SUB);
@@ -469,13 +468,22 @@ __global__ void __launch_bounds__(256) k_mg_capply(MgGeom m, const float2* M, co
   } else if constexpr (DOT == 2) {
     double d[3] = {0.0, 0.0, 0.0};
     if (own) {
-      const float2 a = x[q];
+      const float4 pr = x(q >> 1);
+      const float2 a = (q & 1) ? make_float2(pr.z, pr.w) : make_float2(pr.x, pr.y);
       d[0] = (double)a.x * v.x + (double)a.y * v.y;
       d[1] = (double)a.x * v.y - (double)a.y * v.x;
       d[2] = (double)v.x * v.x + (double)v.y * v.y;
     }
     block_reduce<3>(d, partials + (size_t)blockIdx.x * 3);
   }
+}
+
+template <int SUB, int DOT>
+__global__ void __launch_bounds__(256) k_mg_capply(MgGeom m, const float2* M, const float2* x, float2* y,
+                                                   const float2* w, double* partials, const CoarseState* st) {
+  if (DOT && cs_done(st)) return;
+  const float4* xp = reinterpret_cast<const float4*>(x);
+  capply_body<SUB, DOT>(m, M, [&](size_t k) { return xp[k]; }, y, w, partials);
 }
 
 // x = p = v = 0, r = rhat = b, partial sums of <b, b> as <rhat, r>, <r, r>
@@ -493,11 +501,10 @@ __global__ void __launch_bounds__(256) k_c_start(const float2* b, float2* x, flo
   block_reduce<3>(d, partials + (size_t)blockIdx.x * 3);
 }
 
-// Iteration it: <rhat, r> and |r|^2 from the np records of the last r update,
-// the convergence test, p = r + beta (p - omega v)
-__global__ void __launch_bounds__(256) k_c_p(const float2* r, float2* p, const float2* v, const double* partials,
-                                             int np, CoarseState* st, int it, int max_iters, double tol2, size_t n) {
-  if (cs_done(st)) return;
+// Iteration it: <rhat, r> and |r|^2 from the np records of the last r update and
+// the convergence test (true: stop); p = r + b p + c v with b = beta, c = -beta omega
+__device__ inline bool cs_beta(const double* partials, int np, CoarseState* st, int it, int max_iters, double tol2,
+                               float2& b, float2& c) {
   double s[3];
   sum_partials<3>(partials, np, s);
   const cx<double> rho = {s[0], s[1]};
@@ -519,16 +526,13 @@ __global__ void __launch_bounds__(256) k_c_p(const float2* r, float2* p, const f
     if (it == 0) st->target2 = tol2 * s[2];
     if (stop) cs_stop(st, it);
   }
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (stop || i >= n) return;
-  const float2 b = make_float2((float)beta.r, (float)beta.i), c = make_float2((float)-bo.r, (float)-bo.i);
-  p[i] = fadd(r[i], fadd(fmulc(b, p[i]), fmulc(c, v[i])));
+  b = make_float2((float)beta.r, (float)beta.i);
+  c = make_float2((float)-bo.r, (float)-bo.i);
+  return stop;
 }
 
-// alpha = rho / <rhat, v>, s = r - alpha v
-__global__ void __launch_bounds__(256) k_c_s(const float2* r, const float2* v, float2* s, const double* partials,
-                                             int np, CoarseState* st, int it, size_t n) {
-  if (cs_done(st)) return;
+// alpha = rho / <rhat, v> from the np records of the latter; a = -alpha (true: stop)
+__device__ inline bool cs_alpha(const double* partials, int np, CoarseState* st, int it, float2& a) {
   double d[2];
   sum_partials<2>(partials, np, d);
   const bool stop = d[0] == 0.0 && d[1] == 0.0;
@@ -539,9 +543,74 @@ __global__ void __launch_bounds__(256) k_c_s(const float2* r, const float2* v, f
     st->alpha[1] = ai;
     if (stop) cs_stop(st, it);
   }
+  a = make_float2((float)-ar, (float)-ai);
+  return stop;
+}
+
+__device__ inline float4 pair_fma(float2 f, float4 v, float4 s) {
+  const float2 a = fadd(make_float2(s.x, s.y), fmulc(f, make_float2(v.x, v.y)));
+  const float2 b = fadd(make_float2(s.z, s.w), fmulc(f, make_float2(v.z, v.w)));
+  return make_float4(a.x, a.y, b.x, b.y);
+}
+
+// p = r + beta (p0 - omega v0)
+__global__ void __launch_bounds__(256) k_c_p(const float2* r, const float2* p0, const float2* v0, float2* p,
+                                             const double* partials, int np, CoarseState* st, int it, int max_iters,
+                                             double tol2, size_t n) {
+  if (cs_done(st)) return;
+  float2 b, c;
+  const bool stop = cs_beta(partials, np, st, it, max_iters, tol2, b, c);
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (stop || i >= n) return;
-  s[i] = fadd(r[i], fmulc(make_float2((float)-ar, (float)-ai), v[i]));
+  p[i] = fadd(r[i], fadd(fmulc(b, p0[i]), fmulc(c, v0[i])));
+}
+
+// s = r - alpha v
+__global__ void __launch_bounds__(256) k_c_s(const float2* r, const float2* v, float2* s, const double* partials,
+                                             int np, CoarseState* st, int it, size_t n) {
+  if (cs_done(st)) return;
+  float2 a;
+  const bool stop = cs_alpha(partials, np, st, it, a);
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (stop || i >= n) return;
+  s[i] = fadd(r[i], fmulc(a, v[i]));
+}
+
+// The same with the operator in one launch each, for coarse lattices whose
+// launches cost more than their work: every row forms the elements of p (of s) that
+// it needs from r, p0, v0 (r, v) in the caches and stores its own, so p and v
+// alternate between two buffers. v = D_c p, partial sums of <rhat, v>:
+template <int SUB>
+__global__ void __launch_bounds__(256) k_c_pv(MgGeom m, const float2* M, const float2* r, const float2* p0,
+                                              const float2* v0, float2* p, float2* v, const float2* rh,
+                                              const double* pin, int np, double* pout, CoarseState* st, int it,
+                                              int max_iters, double tol2) {
+  if (cs_done(st)) return;
+  float2 b, c;
+  if (cs_beta(pin, np, st, it, max_iters, tol2, b, c)) return;
+  const float4 *r4 = reinterpret_cast<const float4*>(r), *p4 = reinterpret_cast<const float4*>(p0),
+               *v4 = reinterpret_cast<const float4*>(v0);
+  auto x = [&](size_t k) { return pair_fma(c, v4[k], pair_fma(b, p4[k], r4[k])); };
+  const size_t q = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) / SUB;
+  if (threadIdx.x % SUB == 0 && (q & 1) == 0 && q < (size_t)m.nagg * 2 * m.n)
+    reinterpret_cast<float4*>(p)[q >> 1] = x(q >> 1);
+  capply_body<SUB, 1>(m, M, x, v, rh, pout);
+}
+
+// t = D_c s, partial sums of <s, t> and <t, t>
+template <int SUB>
+__global__ void __launch_bounds__(256) k_c_st(MgGeom m, const float2* M, const float2* r, const float2* v, float2* s,
+                                              float2* t, const double* pin, int np, double* pout, CoarseState* st,
+                                              int it) {
+  if (cs_done(st)) return;
+  float2 a;
+  if (cs_alpha(pin, np, st, it, a)) return;
+  const float4 *r4 = reinterpret_cast<const float4*>(r), *v4 = reinterpret_cast<const float4*>(v);
+  auto x = [&](size_t k) { return pair_fma(a, v4[k], r4[k]); };
+  const size_t q = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) / SUB;
+  if (threadIdx.x % SUB == 0 && (q & 1) == 0 && q < (size_t)m.nagg * 2 * m.n)
+    reinterpret_cast<float4*>(s)[q >> 1] = x(q >> 1);
+  capply_body<SUB, 2>(m, M, x, t, nullptr, pout);
 }
 
 // omega = <t, s> / <t, t> from the np2 records of <s, t>, <t, t>; x += alpha p +
@@ -590,7 +659,7 @@ struct MgState {
   lqcd_mg_params prm{};
   char* B = nullptr;    // n chiral basis fields (FP32, two halves each)
   float2* M = nullptr;  // [nagg][9][n column pairs][2n rows][2]
-  float2* cv[8] = {};   // coarse work vectors
+  float2* cv[10] = {};  // coarse work vectors
   char* f32[4] = {};    // FP32 full fields (two halves)
   double* partials[3] = {};  // records of <rhat, v>; <s, t>, <t, t>; <rhat, r>, |r|^2
   CoarseState* cs = nullptr;
@@ -672,25 +741,46 @@ int capply(lqcd_ctx* c, MgState& s, const float2* x, float2* y, const float2* w 
 // host enqueues as many iterations as the last solve took, then looks, then two
 // at a time (a launch past the end returns at once). Against nine launches and
 // three sums on the host per iteration: multigrid solve on 16^3x32 (7 coarse
-// iterations per solve) 119 -> 72 ms, on 8^3x16 47 -> 27 ms.
+// iterations per solve) 119 -> 72 ms, on 8^3x16 47 -> 27 ms. An iteration is three
+// launches where the rows have 16 lanes, else five: outer iteration of the solve
+// 16^3x32 with five 1.81 ms, with three 1.73; 8^3x16 1.16 and 1.05. With 4 lanes per
+// row a lane would read three vectors for its 36 pairs where it now reads one.
 int coarse_solve(lqcd_ctx* c, MgState& s, int& iters) {
-  float2 *b = s.cv[0], *x = s.cv[1], *r = s.cv[2], *rh = s.cv[3], *p = s.cv[4], *v = s.cv[5], *t = s.cv[6],
-         *q = s.cv[7];
+  float2 *b = s.cv[0], *x = s.cv[1], *r = s.cv[2], *rh = s.cv[3], *t = s.cv[6], *q = s.cv[7];
+  float2 *const p[2] = {s.cv[4], s.cv[8]}, *const v[2] = {s.cv[5], s.cv[9]};  // of even and odd iterations
   const size_t n = s.nc();
   const dim3 grid(grid1(n)), block(256);
   const int nv = grid1(n), na = capply_blocks(s), most = s.prm.coarse_max_iter;
+  const bool one = capply_sub(s) == 16;  // vector updates inside the operator's launches
   const double tol2 = s.prm.coarse_tol * s.prm.coarse_tol;
   hipStream_t st = c->stream;
-  hipLaunchKernelGGL(k_c_start, grid, block, 0, st, b, x, r, rh, p, v, s.partials[2], s.cs, n);
-  hipLaunchKernelGGL(k_c_p, grid, block, 0, st, r, p, v, s.partials[2], nv, s.cs, 0, most, tol2, n);
+  // p and v = D_c p of iteration it
+  auto direction = [&](int it) -> int {
+    const int w = it & 1;
+    if (one) {
+      hipLaunchKernelGGL(k_c_pv<16>, dim3(na), block, 0, st, s.m, s.M, r, p[1 - w], v[1 - w], p[w], v[w], rh,
+                         s.partials[2], nv, s.partials[0], s.cs, it, most, tol2);
+      return LQCD_OK;
+    }
+    hipLaunchKernelGGL(k_c_p, grid, block, 0, st, r, p[1 - w], v[1 - w], p[w], s.partials[2], nv, s.cs, it, most, tol2,
+                       n);
+    return capply<1>(c, s, p[w], v[w], rh, s.partials[0]);
+  };
+  hipLaunchKernelGGL(k_c_start, grid, block, 0, st, b, x, r, rh, p[1], v[1], s.partials[2], s.cs, n);
+  LQ_TRY(direction(0));
   volatile int* done = reinterpret_cast<int*>(c->hscal + 40);  // pinned: done, iters
   for (int it = 0, chunk = s.coarse_last;; chunk = 2) {
     for (int k = 0; k < chunk; ++k, ++it) {
-      LQ_TRY(capply<1>(c, s, p, v, rh, s.partials[0]));
-      hipLaunchKernelGGL(k_c_s, grid, block, 0, st, r, v, q, s.partials[0], na, s.cs, it, n);
-      LQ_TRY(capply<2>(c, s, q, t, nullptr, s.partials[1]));
-      hipLaunchKernelGGL(k_c_xr, grid, block, 0, st, x, p, q, t, r, rh, s.partials[1], na, s.partials[2], s.cs, n);
-      hipLaunchKernelGGL(k_c_p, grid, block, 0, st, r, p, v, s.partials[2], nv, s.cs, it + 1, most, tol2, n);
+      if (one) {
+        hipLaunchKernelGGL(k_c_st<16>, dim3(na), block, 0, st, s.m, s.M, r, v[it & 1], q, t, s.partials[0], na,
+                           s.partials[1], s.cs, it);
+      } else {
+        hipLaunchKernelGGL(k_c_s, grid, block, 0, st, r, v[it & 1], q, s.partials[0], na, s.cs, it, n);
+        LQ_TRY(capply<2>(c, s, q, t, nullptr, s.partials[1]));
+      }
+      hipLaunchKernelGGL(k_c_xr, grid, block, 0, st, x, p[it & 1], q, t, r, rh, s.partials[1], na, s.partials[2], s.cs,
+                         n);
+      LQ_TRY(direction(it + 1));
     }
     LQ_HIP(hipGetLastError());
     LQ_HIP(hipMemcpyAsync(const_cast<int*>(done), &s.cs->done, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
