@@ -647,11 +647,16 @@ __global__ void __launch_bounds__(256) k_flat_axpy(void* out, const void* a, con
 // The CG update in one pass: x += alpha p, r -= alpha q, and the
 // per-workgroup partial sums of |r|^2 in FP64 (slot 1 of each pair, as k_flat_dot)
 template <int P>
-__global__ void __launch_bounds__(256) k_flat_xr(void* x, const void* p, void* r, const void* q, const CgState* st,
-                                                 double* partials, size_t n) {
+__global__ void __launch_bounds__(256) k_flat_xr(void* x, const void* p, void* r, const void* q, CgState* st,
+                                                 const double* in, int nfold, int it, double* partials, size_t n) {
   using T = typename IO<P>::T;
   if (st->done) return;
-  const double alpha = st->alpha;
+  double alpha = 0.0;
+  if (nfold) {
+    if (!cg_alpha_of(st, in, nfold, 1, it, blockIdx.x == 0 && threadIdx.x == 0, alpha)) return;
+  } else {
+    alpha = st->alpha;
+  }
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[2] = {0.0, 0.0};
   if (i < n) {
@@ -826,6 +831,13 @@ struct DWork {
     for (void* p : mem) (void)hipFree(p);
     if (partials) (void)hipFree(partials);
   }
+  size_t npairs = 0;
+  // two sets of n pairs of partial sums: <p, A p> and |r|^2
+  int alloc_pairs(size_t n) {
+    LQ_HIP(hipMalloc(&partials, n * 4 * sizeof(double)));
+    npairs = n;
+    return LQCD_OK;
+  }
   int alloc(lqcd_ctx* c, size_t bytes, void** p) {
     if (hipMalloc(p, bytes) != hipSuccess) {
       (void)hipGetLastError();
@@ -868,12 +880,17 @@ int cg_solve(lqcd_ctx* c, DWork& w, size_t n, size_t ngroups, void* x, void* p, 
   if (prec == 0) hipLaunchKernelGGL(k_flat_dot<0>, dim3(nb), dim3(256), 0, c->stream, r, r, w.partials, n);
   else hipLaunchKernelGGL(k_flat_dot<1>, dim3(nb), dim3(256), 0, c->stream, r, r, w.partials, n);
   LQ_TRY(cg_init(c, w.partials, nb, target, max_iters));
-  return cg_run(c, [&]() -> int {
+  const double* pq = w.partials;
+  double* rr = w.partials + w.npairs * 2;
+  const int nfold = fold_ok((int)ngroups) ? (int)ngroups : 0;
+  return cg_run(c, [&](int it) -> int {
     LQ_TRY(normal());
-    LQ_TRY(cg_alpha(c, w.partials, ngroups, 1));
-    if (prec == 0) hipLaunchKernelGGL(k_flat_xr<0>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, st, w.partials, n);
-    else hipLaunchKernelGGL(k_flat_xr<1>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, st, w.partials, n);
-    return cg_beta(c, w.partials, nb);
+    if (!nfold) LQ_TRY(cg_alpha(c, pq, ngroups, 1, it));
+    if (prec == 0)
+      hipLaunchKernelGGL(k_flat_xr<0>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, st, pq, nfold, it, rr, n);
+    else
+      hipLaunchKernelGGL(k_flat_xr<1>, dim3(nb), dim3(256), 0, c->stream, x, p, r, q, st, pq, nfold, it, rr, n);
+    return cg_beta(c, rr, nb, it);
   }, iters);
 }
 
@@ -901,7 +918,7 @@ int dwf_solve(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params& pr
   for (void** f : {&bn, &r, &p, &q, &t, &ph}) LQ_TRY(w.alloc(c, bytes, f));
   // pairs for the flat reductions (one per 256 sites) and for the norm of D p (one per operator workgroup)
   const size_t ngroups = dwf_apply_groups(c->g, d.Ls);
-  LQ_HIP(hipMalloc(&w.partials, std::max((size_t)(n + 255) / 256, ngroups) * 2 * sizeof(double)));
+  LQ_TRY(w.alloc_pairs(std::max((size_t)(n + 255) / 256, ngroups)));
   double bb = 0.0;
   LQ_TRY(dot(c, w, n, b, b, nullptr, &bb));
   const double bnorm = std::sqrt(bb);
@@ -1192,7 +1209,7 @@ int dwf_solve_eo(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params&
   }
   // pairs for the flat reductions (one per 256 sites) and for the norm of S p (one per operator workgroup)
   const size_t npairs = std::max({(size_t)(nf + 255) / 256, (size_t)e.grid.x, mixed ? (size_t)e32.grid.x : 0});
-  LQ_HIP(hipMalloc(&w.partials, npairs * 2 * sizeof(double)));
+  LQ_TRY(w.alloc_pairs(npairs));
   auto ev = [](void* f) { return f; };  // even half = start of the field
   double bb = 0.0;
   LQ_TRY(dot(c, w, nf, b, b, nullptr, &bb));

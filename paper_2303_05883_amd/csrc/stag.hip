@@ -238,24 +238,24 @@ __global__ void __launch_bounds__(SBS) k_stag_dot(const void* a, const void* b, 
   block_reduce<2>(v, partials + (size_t)blockIdx.x * 2);
 }
 
-// CG update in one pass: x += alpha p, r -= alpha q, per-workgroup pairs
-// (0, |r|^2) of the updated r (FP64 sums)
+// CG, iteration it: r -= alpha q, partial sums of |r|^2 (slot 1 of the pairs in
+// out). With nfold, alpha is formed from the nfold pairs of in, else it is the state's.
 template <int P>
-__global__ void __launch_bounds__(SBS) k_stag_xr(void* x, const void* p, void* r, const void* q, const CgState* st,
-                                                 double* partials, size_t vh) {
+__global__ void __launch_bounds__(SBS) k_stag_r(void* r, const void* q, CgState* st, const double* in, int nfold, int it,
+                                                double* out, size_t vh) {
   using T = typename SIO<P>::T;
   if (st->done) return;
-  const double alpha = st->alpha;
+  double alpha = 0.0;
+  if (nfold) {
+    if (!cg_alpha_of(st, in, nfold, 0, it, blockIdx.x == 0 && threadIdx.x == 0, alpha)) return;
+  } else {
+    alpha = st->alpha;
+  }
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double v[2] = {0.0, 0.0};
   if (i < vh) {
-    const T al = (T)alpha, mal = (T)(-alpha);
+    const T mal = (T)(-alpha);
     cx<T> a[3], b[3];
-    SIO<P>::load(x, i, a);
-    SIO<P>::load(p, i, b);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) a[k] = a[k] + al * b[k];
-    SIO<P>::store(x, i, a);
     SIO<P>::load(r, i, a);
     SIO<P>::load(q, i, b);
 #pragma unroll
@@ -265,20 +265,27 @@ __global__ void __launch_bounds__(SBS) k_stag_xr(void* x, const void* p, void* r
     }
     SIO<P>::store(r, i, a);
   }
-  block_reduce<2>(v, partials + (size_t)blockIdx.x * 2);
+  block_reduce<2>(v, out + (size_t)blockIdx.x * 2);
 }
 
-// CG direction: p = r + beta p
+// CG, iteration it: x += alpha p and the next direction p = r + beta p (p read once
+// for both), beta from the nfold pairs of in or the state's
 template <int P>
-__global__ void __launch_bounds__(SBS) k_stag_p(void* p, const void* r, const CgState* st, size_t vh) {
+__global__ void __launch_bounds__(SBS) k_stag_xp(void* x, void* p, const void* r, CgState* st, const double* in,
+                                                 int nfold, int it, size_t vh) {
   using T = typename SIO<P>::T;
-  if (st->done) return;
+  if (st->last < it) return;
+  const double bt = nfold ? cg_beta_of(st, in, nfold, it, blockIdx.x == 0 && threadIdx.x == 0) : st->beta;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= vh) return;
-  const T beta = (T)st->beta;
+  const T al = (T)st->alpha, beta = (T)bt;
   cx<T> a[3], b[3];
-  SIO<P>::load(r, i, a);
+  SIO<P>::load(x, i, a);
   SIO<P>::load(p, i, b);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) a[k] = a[k] + al * b[k];
+  SIO<P>::store(x, i, a);
+  SIO<P>::load(r, i, a);
 #pragma unroll
   for (int k = 0; k < 3; ++k) a[k] = a[k] + beta * b[k];
   SIO<P>::store(p, i, a);
@@ -391,20 +398,21 @@ int dot(lqcd_ctx* c, SWork& w, const void* a, const void* b, double* ab, double*
   return cg_sum_host(c, w.partials, nb, ab, bb);
 }
 
-// One CG iteration on q = (m^2 - H_eo H_oe) p in precision prec: the operator
-// with Re <p, q>, alpha, x += alpha p and r -= alpha q with |r|^2, beta and the
-// convergence test, p = r + beta p
-int cg_iteration(lqcd_ctx* c, SWork& w, double mass, int prec, void* x, void* r, void* p, void* q, void* t) {
-  const int nb = grid_for_sites(c->g.vh);
+// CG iteration it on q = (m^2 - H_eo H_oe) p in precision prec: the operator with
+// Re <p, q>, alpha, r -= alpha q with |r|^2, beta and the convergence test, x +=
+// alpha p and p = r + beta p
+int cg_iteration(lqcd_ctx* c, SWork& w, double mass, int prec, void* x, void* r, void* p, void* q, void* t, int it) {
+  const int nb = grid_for_sites(c->g.vh), nfold = fold_ok(nb) ? nb : 0;
   const size_t vh = c->g.vh;
   CgState* st = cg_state(c);
-  LQ_TRY(stag_schur(c, prec, mass, p, t, q, w.partials, st));
-  LQ_TRY(cg_alpha(c, w.partials, nb, 0));
-  if (prec == 0) hipLaunchKernelGGL(k_stag_xr<0>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, q, st, w.partials, vh);
-  else hipLaunchKernelGGL(k_stag_xr<1>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, q, st, w.partials, vh);
-  LQ_TRY(cg_beta(c, w.partials, nb));
-  if (prec == 0) hipLaunchKernelGGL(k_stag_p<0>, dim3(nb), dim3(SBS), 0, c->stream, p, r, st, vh);
-  else hipLaunchKernelGGL(k_stag_p<1>, dim3(nb), dim3(SBS), 0, c->stream, p, r, st, vh);
+  double *pq = w.partials, *rr = w.partials + (size_t)nb * 2;
+  LQ_TRY(stag_schur(c, prec, mass, p, t, q, pq, st));
+  if (!nfold) LQ_TRY(cg_alpha(c, pq, nb, 0, it));
+  if (prec == 0) hipLaunchKernelGGL(k_stag_r<0>, dim3(nb), dim3(SBS), 0, c->stream, r, q, st, pq, nfold, it, rr, vh);
+  else hipLaunchKernelGGL(k_stag_r<1>, dim3(nb), dim3(SBS), 0, c->stream, r, q, st, pq, nfold, it, rr, vh);
+  if (!nfold) LQ_TRY(cg_beta(c, rr, nb, it));
+  if (prec == 0) hipLaunchKernelGGL(k_stag_xp<0>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, st, rr, nfold, it, vh);
+  else hipLaunchKernelGGL(k_stag_xp<1>, dim3(nb), dim3(SBS), 0, c->stream, x, p, r, st, rr, nfold, it, vh);
   LQ_HIP(hipGetLastError());
   return LQCD_OK;
 }
@@ -418,7 +426,7 @@ int cg_solve(lqcd_ctx* c, SWork& w, double mass, int prec, void* x, void* r, voi
   if (prec == 0) hipLaunchKernelGGL(k_stag_dot<0>, dim3(nb), dim3(SBS), 0, c->stream, r, r, w.partials, vh);
   else hipLaunchKernelGGL(k_stag_dot<1>, dim3(nb), dim3(SBS), 0, c->stream, r, r, w.partials, vh);
   LQ_TRY(cg_init(c, w.partials, nb, target, max_iters));
-  return cg_run(c, [&] { return cg_iteration(c, w, mass, prec, x, r, p, q, t); }, iters);
+  return cg_run(c, [&](int it) { return cg_iteration(c, w, mass, prec, x, r, p, q, t, it); }, iters);
 }
 
 int down(lqcd_ctx* c, const void* in64, void* out32) {
@@ -457,7 +465,7 @@ int stag_solve(lqcd_ctx* c, double mass, const lqcd_solve_params& prm, const voi
   void *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *t32 = nullptr, *e32 = nullptr;
   if (mixed)
     for (void** f : {&r32, &p32, &q32, &t32, &e32}) LQ_TRY(w.alloc(stag_field_bytes(1, c->g.vh), f));
-  LQ_HIP(hipMalloc(&w.partials, (size_t)grid_for_sites(c->g.vh) * 2 * sizeof(double)));
+  LQ_HIP(hipMalloc(&w.partials, (size_t)grid_for_sites(c->g.vh) * 4 * sizeof(double)));
   // full-lattice |b|
   double bb_e = 0.0, bb_o = 0.0;
   LQ_TRY(dot(c, w, b_e, b_e, nullptr, &bb_e));
