@@ -69,6 +69,51 @@ static void dfree(void*& p) {
   p = nullptr;
 }
 
+void pool_release(lqcd_ctx* c, size_t keep) {
+  size_t n = 0;
+  for (; n < c->pool.size() && c->pool_bytes > keep; ++n) {
+    (void)hipFree(c->pool[n].first);
+    c->pool_bytes -= c->pool[n].second;
+  }
+  c->pool.erase(c->pool.begin(), c->pool.begin() + n);
+}
+
+int Scratch::get(size_t bytes, void** p, const char* what) {
+  auto& pool = c_->pool;
+  mem_.reserve(mem_.size() + 1);
+  for (size_t k = pool.size(); k-- > 0;)
+    if (pool[k].second == bytes) {
+      *p = pool[k].first;
+      pool.erase(pool.begin() + k);
+      c_->pool_bytes -= bytes;
+      mem_.emplace_back(*p, bytes);
+      return LQCD_OK;
+    }
+  if (hipMalloc(p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    pool_release(c_);
+    if (hipMalloc(p, bytes) != hipSuccess) {
+      *p = nullptr;
+      (void)hipGetLastError();
+      return set_error(LQCD_ENOMEM, what);
+    }
+  }
+  mem_.emplace_back(*p, bytes);
+  return LQCD_OK;
+}
+
+Scratch::~Scratch() {
+  for (auto& m : mem_) {
+    if (m.second > POOL_MAX) {
+      (void)hipFree(m.first);
+      continue;
+    }
+    pool_release(c_, POOL_MAX - m.second);
+    c_->pool.push_back(m);
+    c_->pool_bytes += m.second;
+  }
+}
+
 static size_t full_sites(const lqcd_ctx* c) { return (size_t)c->g.vh * 2; }
 
 int ensure_canon(lqcd_ctx* c) {
@@ -231,6 +276,7 @@ int lqcd_destroy(lqcd_ctx* c) {
     dfree(c->half_c[p]);
     dfree(c->half_d[p]);
   }
+  pool_release(c);
   dfree(c->canon_a);
   dfree(c->canon_b);
   dfree(c->sap_res);
@@ -499,14 +545,10 @@ int lqcd_stag_apply(lqcd_ctx* c, int op, int prec, double mass, const double* in
   double* dout = on_device ? out : reinterpret_cast<double*>(c->canon_b);
   const size_t hb = stag_field_bytes(prec, c->g.vh);
   void* h[5] = {};
+  Scratch mem(c);
   int st = LQCD_OK;
-  for (auto& p : h) {
-    if (hipMalloc(&p, hb) != hipSuccess) {
-      (void)hipGetLastError();
-      st = set_error(LQCD_ENOMEM, "staggered apply buffers");
-      break;
-    }
-  }
+  for (auto& p : h)
+    if (st == LQCD_OK) st = mem.get(hb, &p, "staggered apply buffers");
   if (st == LQCD_OK) st = stag_import(c, prec, 0, din, h[0]);
   if (st == LQCD_OK) st = stag_import(c, prec, 1, din, h[1]);
   if (st == LQCD_OK && op == LQCD_STAG_D) {
@@ -524,8 +566,6 @@ int lqcd_stag_apply(lqcd_ctx* c, int op, int prec, double mass, const double* in
       st = set_error(LQCD_EHIP, "copy back");
   }
   if (hipStreamSynchronize(c->stream) != hipSuccess && st == LQCD_OK) st = set_error(LQCD_EHIP, "synchronise");
-  for (void* p : h)
-    if (p) (void)hipFree(p);
   return st;
 }
 
@@ -547,14 +587,10 @@ int lqcd_stag_solve(lqcd_ctx* c, double mass, const double* b, double* x, const 
   LQ_TRY(check_finite(c, db, full_sites(c) * 6));
   const size_t hb = stag_field_bytes(0, c->g.vh);
   void* h[4] = {};
+  Scratch mem(c);
   int st = LQCD_OK;
-  for (auto& p : h) {
-    if (hipMalloc(&p, hb) != hipSuccess) {
-      (void)hipGetLastError();
-      st = set_error(LQCD_ENOMEM, "staggered solve buffers");
-      break;
-    }
-  }
+  for (auto& p : h)
+    if (st == LQCD_OK) st = mem.get(hb, &p, "staggered solve buffers");
   if (st == LQCD_OK) st = stag_import(c, 0, 0, db, h[0]);
   if (st == LQCD_OK) st = stag_import(c, 0, 1, db, h[1]);
   lqcd_solve_stats ss{};
@@ -572,8 +608,6 @@ int lqcd_stag_solve(lqcd_ctx* c, double mass, const double* b, double* x, const 
     }
   }
   if (hipStreamSynchronize(c->stream) != hipSuccess && status == LQCD_OK) status = set_error(LQCD_EHIP, "synchronise");
-  for (void* p : h)
-    if (p) (void)hipFree(p);
   if (stats) *stats = ss;
   return status;
 }
@@ -586,18 +620,12 @@ static int validate_dwf(const lqcd_dwf_params* d) {
   return LQCD_OK;
 }
 
-// device buffers freed on scope exit
+// zeroed device buffers for the rest of the call
 struct Bufs {
-  std::vector<void*> p;
-  ~Bufs() {
-    for (void* q : p) (void)hipFree(q);
-  }
+  Scratch mem;
+  explicit Bufs(lqcd_ctx* c) : mem(c) {}
   int get(lqcd_ctx* c, size_t bytes, void** out) {
-    if (hipMalloc(out, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "device buffer allocation failed");
-    }
-    p.push_back(*out);
+    LQ_TRY(mem.get(bytes, out, "device buffer allocation failed"));
     LQ_HIP(hipMemsetAsync(*out, 0, bytes, c->stream));
     return LQCD_OK;
   }
@@ -612,7 +640,7 @@ int lqcd_dwf_apply(lqcd_ctx* c, const lqcd_dwf_params* d, int dag, int prec, con
   if (!c->have_gauge) return set_error(LQCD_ESTATE, "set_gauge must come first");
   const size_t cbytes = full_sites(c) * 192 * (size_t)d->Ls;
   const size_t fb = dwf_field_bytes(prec, c->g.vh, d->Ls);
-  Bufs b;
+  Bufs b(c);
   void *cin = nullptr, *cout = nullptr, *f[3];
   const double* din = in;
   double* dout = out;
@@ -643,7 +671,7 @@ int lqcd_dwf_solve(lqcd_ctx* c, const lqcd_dwf_params* d, const double* b, doubl
   if (!c->have_gauge) return set_error(LQCD_ESTATE, "set_gauge must come first");
   const size_t cbytes = full_sites(c) * 192 * (size_t)d->Ls;
   const size_t fb = dwf_field_bytes(0, c->g.vh, d->Ls);
-  Bufs bf;
+  Bufs bf(c);
   void *cb = nullptr, *cx_ = nullptr, *fbn, *fx;
   const double* db = b;
   double* dx = x;
@@ -677,7 +705,7 @@ int lqcd_dwf_apply_schur(lqcd_ctx* c, const lqcd_dwf_params* d, int dag, int pre
   if (!c->have_gauge) return set_error(LQCD_ESTATE, "set_gauge must come first");
   const size_t cbytes = full_sites(c) * 192 * (size_t)d->Ls;
   const size_t fb = dwf_field_bytes(prec, c->g.vh, d->Ls);
-  Bufs b;
+  Bufs b(c);
   void *cin = nullptr, *cout = nullptr, *f[4];
   const double* din = in;
   double* dout = out;
@@ -710,7 +738,7 @@ int lqcd_dwf_solve_eo(lqcd_ctx* c, const lqcd_dwf_params* d, const double* b, do
   if (!c->have_gauge) return set_error(LQCD_ESTATE, "set_gauge must come first");
   const size_t cbytes = full_sites(c) * 192 * (size_t)d->Ls;
   const size_t fb = dwf_field_bytes(0, c->g.vh, d->Ls);
-  Bufs bf;
+  Bufs bf(c);
   void *cb = nullptr, *cx_ = nullptr, *fbn, *fx;
   const double* db = b;
   double* dx = x;
@@ -781,7 +809,7 @@ int lqcd_mg_setup(lqcd_ctx* c, const lqcd_mg_params* mp, const double* start, in
   if (!c->have_gauge || !c->have_clover) return set_error(LQCD_ESTATE, "set_gauge and set_clover must come first");
   LQ_TRY(ensure_apply_buffers(c, 1));
   const size_t n = full_sites(c) * 24 * (size_t)mp->nvec;
-  Bufs bf;
+  Bufs bf(c);
   const double* ds = start;
   if (!on_device) {
     void* d = nullptr;
@@ -847,7 +875,7 @@ int lqcd_mg_restrict(lqcd_ctx* c, const double* fine, double* coarse, int on_dev
   if (!c || !fine || !coarse) return set_error(LQCD_EINVAL, "null argument");
   if (!c->mg) return set_error(LQCD_ESTATE, "lqcd_mg_setup must come first");
   LQ_TRY(mg_stage_fine(c, fine, on_device));
-  Bufs bf;
+  Bufs bf(c);
   void* rc = nullptr;
   LQ_TRY(bf.get(c, mg_coarse_size(c) * 8, &rc));
   LQ_TRY(mg_restrict(c, c->half_a[1], c->half_b[1], rc));
@@ -858,7 +886,7 @@ int lqcd_mg_prolong(lqcd_ctx* c, const double* coarse, double* fine, int on_devi
   if (!c || !fine || !coarse) return set_error(LQCD_EINVAL, "null argument");
   if (!c->mg) return set_error(LQCD_ESTATE, "lqcd_mg_setup must come first");
   LQ_TRY(ensure_apply_buffers(c, 1));
-  Bufs bf;
+  Bufs bf(c);
   void* ec = nullptr;
   LQ_TRY(mg_stage_coarse(c, bf, coarse, on_device, &ec));
   LQ_TRY(mg_prolong(c, ec, c->half_c[1], c->half_d[1]));
@@ -868,7 +896,7 @@ int lqcd_mg_prolong(lqcd_ctx* c, const double* coarse, double* fine, int on_devi
 int lqcd_mg_coarse_apply(lqcd_ctx* c, const double* in, double* out, int on_device) {
   if (!c || !in || !out) return set_error(LQCD_EINVAL, "null argument");
   if (!c->mg) return set_error(LQCD_ESTATE, "lqcd_mg_setup must come first");
-  Bufs bf;
+  Bufs bf(c);
   void *x = nullptr, *y = nullptr;
   LQ_TRY(mg_stage_coarse(c, bf, in, on_device, &x));
   LQ_TRY(bf.get(c, mg_coarse_size(c) * 8, &y));

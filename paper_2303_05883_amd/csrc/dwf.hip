@@ -825,25 +825,18 @@ int dwf_apply(lqcd_ctx* c, int prec, const lqcd_dwf_params& d, int dag, const vo
 namespace {
 
 struct DWork {
-  std::vector<void*> mem;
+  Scratch mem;
   double* partials = nullptr;
-  ~DWork() {
-    for (void* p : mem) (void)hipFree(p);
-    if (partials) (void)hipFree(partials);
-  }
   size_t npairs = 0;
+  explicit DWork(lqcd_ctx* c) : mem(c) {}
   // two sets of n pairs of partial sums: <p, A p> and |r|^2
   int alloc_pairs(size_t n) {
-    LQ_HIP(hipMalloc(&partials, n * 4 * sizeof(double)));
     npairs = n;
-    return LQCD_OK;
+    return mem.get(n * 4 * sizeof(double), reinterpret_cast<void**>(&partials),
+                   "domain-wall solver workspace allocation failed");
   }
   int alloc(lqcd_ctx* c, size_t bytes, void** p) {
-    if (hipMalloc(p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "domain-wall solver workspace allocation failed");
-    }
-    mem.push_back(*p);
+    LQ_TRY(mem.get(bytes, p, "domain-wall solver workspace allocation failed"));
     // padding sites must read as zero in the flat vector kernels
     LQ_HIP(hipMemsetAsync(*p, 0, bytes, c->stream));
     return LQCD_OK;
@@ -912,7 +905,7 @@ int dwf_solve(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params& pr
               lqcd_solve_stats& st) {
   using clk = std::chrono::steady_clock;
   const auto t0 = clk::now();
-  DWork w;
+  DWork w(c);
   const size_t bytes = dwf_field_bytes(0, c->g.vh, d.Ls), n = 2 * padded_sites((size_t)c->g.vh * d.Ls);
   void *bn, *r, *p, *q, *t, *ph;
   for (void** f : {&bn, &r, &p, &q, &t, &ph}) LQ_TRY(w.alloc(c, bytes, f));
@@ -1191,7 +1184,7 @@ int dwf_solve_eo(lqcd_ctx* c, const lqcd_dwf_params& d, const lqcd_solve_params&
   LQ_TRY(m.upload(c, d));
   EoCtx e;
   LQ_TRY(eo_setup(c, 0, d, m.p, e));
-  DWork w;
+  DWork w(c);
   const size_t bytes = dwf_field_bytes(0, c->g.vh, d.Ls);
   const size_t nh = padded_sites((size_t)c->g.vh * d.Ls), nf = 2 * nh;
   void *bp, *r, *pv, *q, *sx, *tA, *tB, *res;

@@ -458,21 +458,11 @@ struct Pair {
 };
 
 struct FWork {
-  std::vector<void*> mem;
+  Scratch mem;
   double* partials = nullptr;
   std::vector<double> host;
-  ~FWork() {
-    for (void* p : mem) (void)hipFree(p);
-    if (partials) (void)hipFree(partials);
-  }
-  int alloc(size_t bytes, void** p) {
-    if (hipMalloc(p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "SAP solver workspace allocation failed");
-    }
-    mem.push_back(*p);
-    return LQCD_OK;
-  }
+  explicit FWork(lqcd_ctx* c) : mem(c) {}
+  int alloc(size_t bytes, void** p) { return mem.get(bytes, p, "SAP solver workspace allocation failed"); }
 };
 
 int grid_of(size_t n) { return (int)((n + LBS - 1) / LBS); }
@@ -519,7 +509,7 @@ int solve_flexible(lqcd_ctx* c, const lqcd_solve_params& prm, const FlexPrecond&
                    const void* b_e, const void* b_o, void* x_e, void* x_o, bool zero_x, lqcd_solve_stats& st) {
   using clk = std::chrono::steady_clock;
   const auto t0 = clk::now();
-  FWork w;
+  FWork w(c);
   const size_t b64 = spinor_bytes(0, c->g.vh);
   Pair r, rh, p, v, s, t, ph, sh, ax;
   for (Pair* q : {&r, &rh, &p, &v, &s, &t, &ax})
@@ -534,7 +524,7 @@ int solve_flexible(lqcd_ctx* c, const lqcd_solve_params& prm, const FlexPrecond&
     for (Pair* q : {&ph, &sh})
       for (auto& h : q->h) LQ_TRY(w.alloc(b64, &h));
   }
-  LQ_HIP(hipMalloc(&w.partials, (size_t)2 * grid_of(c->g.vh) * 3 * sizeof(double)));
+  LQ_TRY(w.alloc((size_t)2 * grid_of(c->g.vh) * 3 * sizeof(double), reinterpret_cast<void**>(&w.partials)));
   Pair b, x;
   b.h[0] = const_cast<void*>(b_e);
   b.h[1] = const_cast<void*>(b_o);
@@ -640,7 +630,7 @@ int solve_sap(lqcd_ctx* c, const lqcd_solve_params& prm, const int blk[4], int n
               const void* b_o, void* x_e, void* x_o, bool zero_x, lqcd_solve_stats& st) {
   if (!sap_shape_ok(c->g, blk)) return set_error(LQCD_EINVAL, "bad SAP block shape");
   const size_t b32 = spinor_bytes(1, c->g.vh);
-  FWork w;
+  FWork w(c);
   Pair e32, q32;
   for (Pair* q : {&e32, &q32})
     for (auto& h : q->h) LQ_TRY(w.alloc(b32, &h));

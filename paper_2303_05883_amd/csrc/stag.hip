@@ -362,20 +362,10 @@ int stag_hop(lqcd_ctx* c, int prec, int out_parity, const void* in, const void* 
 namespace {
 
 struct SWork {
-  std::vector<void*> mem;
+  Scratch mem;
   double* partials = nullptr;
-  ~SWork() {
-    for (void* p : mem) (void)hipFree(p);
-    if (partials) (void)hipFree(partials);
-  }
-  int alloc(size_t bytes, void** p) {
-    if (hipMalloc(p, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "staggered solver workspace allocation failed");
-    }
-    mem.push_back(*p);
-    return LQCD_OK;
-  }
+  explicit SWork(lqcd_ctx* c) : mem(c) {}
+  int alloc(size_t bytes, void** p) { return mem.get(bytes, p, "staggered solver workspace allocation failed"); }
 };
 
 // The vector operations on half fields of precision prec (0 FP64, 1 FP32)
@@ -455,7 +445,7 @@ int stag_solve(lqcd_ctx* c, double mass, const lqcd_solve_params& prm, const voi
                void* x_o, lqcd_solve_stats& st) {
   using clk = std::chrono::steady_clock;
   const auto t0 = clk::now();
-  SWork w;
+  SWork w(c);
   const size_t bytes = stag_field_bytes(0, c->g.vh);
   void *be2, *r, *p, *q, *t;
   for (void** f : {&be2, &r, &p, &q, &t}) LQ_TRY(w.alloc(bytes, f));
@@ -465,7 +455,7 @@ int stag_solve(lqcd_ctx* c, double mass, const lqcd_solve_params& prm, const voi
   void *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *t32 = nullptr, *e32 = nullptr;
   if (mixed)
     for (void** f : {&r32, &p32, &q32, &t32, &e32}) LQ_TRY(w.alloc(stag_field_bytes(1, c->g.vh), f));
-  LQ_HIP(hipMalloc(&w.partials, (size_t)grid_for_sites(c->g.vh) * 4 * sizeof(double)));
+  LQ_TRY(w.alloc((size_t)grid_for_sites(c->g.vh) * 4 * sizeof(double), reinterpret_cast<void**>(&w.partials)));
   // full-lattice |b|
   double bb_e = 0.0, bb_o = 0.0;
   LQ_TRY(dot(c, w, b_e, b_e, nullptr, &bb_e));
