@@ -24,9 +24,12 @@ struct Scal {
 // The partial sums of a reduction that the vector update after it is to add by
 // itself (n records), or none (n = 0: a finalize kernel has done it). Every
 // workgroup adds all records in the same order and forms the scalar for itself;
-// workgroup 0 writes what later launches read, never what its own launch reads:
-// the direction update reads rho and leaves the new one in next, the s update
-// of the next iteration reads next and writes rho.
+// workgroup 0 writes what later launches read, and of what its own launch reads
+// only done: the direction update reads rho and leaves the new one in next, the s
+// update of the next iteration reads next and writes rho. done is read once per
+// workgroup (group_flag): one that finds it set, and would have formed the same end
+// from its sums, only leaves earlier. At the iteration limit it leaves p as it was,
+// which nothing reads any more.
 struct Fold {
   const double* partials = nullptr;
   int n = 0;

@@ -18,14 +18,13 @@ namespace {
 constexpr int BS = 256;
 constexpr int FBS = 1024;  // threads of the one-block finalize kernels
 
-__device__ inline bool is_done(const Scal* s) {
-  return s && __hip_atomic_load(&s->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-}
+// done, in a launch that may set it itself (fold: before the barriers of its sums) or not
+__device__ inline bool is_done(const Scal* s, bool fold) { return fold ? group_flag(&s->done) : s->done != 0; }
 
 // p = r + beta (p - omega v); with f, after forming beta from the sums of <rhat, r>, <r, r>
 template <int P>
 __global__ void __launch_bounds__(BS) k_p_update(const void* r, void* p, const void* v, Scal* sc, Fold f, size_t vh) {
-  if (is_done(sc)) return;
+  if (is_done(sc, f.n != 0)) return;
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
   cx<double> beta = {sc->beta_r, sc->beta_i};
   if (f.n) {
@@ -46,7 +45,7 @@ __global__ void __launch_bounds__(BS) k_p_update(const void* r, void* p, const v
 // s = r - alpha v; with f, after forming alpha from the sums of <rhat, v>
 template <int P>
 __global__ void __launch_bounds__(BS) k_s_update(const void* r, const void* v, void* s, Scal* sc, Fold f, size_t vh) {
-  if (is_done(sc)) return;
+  if (is_done(sc, f.n != 0)) return;
   cx<double> alpha = {sc->alpha_r, sc->alpha_i};
   if (f.n) {
     const cx<double> rho = {sc->next_r, sc->next_i};
@@ -74,7 +73,7 @@ __global__ void __launch_bounds__(BS) k_s_update(const void* r, const void* v, v
 template <int P, int PX>
 __global__ void __launch_bounds__(BS) k_xr_update(void* x, const void* p, const void* s, const void* t, void* r,
                                                   const void* rhat, Scal* sc, Fold f, double* partials, size_t vh) {
-  if (is_done(sc)) return;
+  if (is_done(sc, f.n != 0)) return;
   cx<double> omega = {sc->omega_r, sc->omega_i};
   if (f.n) {
     double d[3];

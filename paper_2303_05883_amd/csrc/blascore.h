@@ -150,6 +150,20 @@ __device__ inline void sum_partials(const double* partials, int n, double out[W]
   __syncthreads();
 }
 
+// A stop flag that a launch both tests and (workgroup 0) may set: one lane reads it
+// and the workgroup decides as one, so that either all of its waves meet the
+// barriers of sum_partials or none does. The setter does it after those barriers.
+// Called at most once per kernel, ahead of any other barrier.
+__device__ inline bool group_flag(const int* flag) {
+  __shared__ int f;
+  if (threadIdx.x == 0) f = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return f != 0;
+}
+__device__ inline void set_flag(int* flag) {
+  __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The scalar updates of one BiCGStab. *_of form the values from the sums v (any
 // thread may), scal_* store them (one thread).
 // alpha = rho / <rhat, v>; false when <rhat, v> vanishes
@@ -161,7 +175,7 @@ __device__ inline bool alpha_of(cx<double> rho, const double v[2], cx<double>& a
 
 __device__ inline void scal_stop(Scal* sc, bool breakdown) {
   if (breakdown) sc->breakdown = 1;
-  __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  set_flag(&sc->done);
 }
 
 __device__ inline void scal_alpha(Scal* sc, const double v[2]) {

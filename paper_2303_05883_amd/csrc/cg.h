@@ -52,7 +52,8 @@ __global__ void __launch_bounds__(CG_FIN) k_cg_init(CgState* st, const double* p
 
 // Iteration it: alpha = |r|^2 / <p, A p> from the n pairs (component comp); false
 // when <p, A p> is not positive, which ends the solve. The writer (one thread of the
-// launch) stores them; what others of the launch read is not written in it.
+// launch) stores them; of what others of the launch read it writes only done, which
+// they test by group_flag.
 __device__ inline bool cg_alpha_of(CgState* st, const double* partials, int n, int comp, int it, bool writer,
                                    double& alpha) {
   double v[2];
@@ -65,7 +66,7 @@ __device__ inline bool cg_alpha_of(CgState* st, const double* partials, int n, i
       st->alpha = alpha;
     } else {
       st->last = it - 1;
-      st->done = 1;
+      set_flag(&st->done);
     }
   }
   return ok;
@@ -83,7 +84,7 @@ __device__ inline double cg_beta_of(CgState* st, const double* partials, int n, 
     st->rr[(it + 1) & 1] = rn;
     if (sqrt(rn) <= st->target || it + 1 >= st->max_iters) {
       st->last = it;
-      st->done = 1;
+      set_flag(&st->done);
     }
   }
   return beta;

@@ -650,7 +650,7 @@ template <int P>
 __global__ void __launch_bounds__(256) k_flat_xr(void* x, const void* p, void* r, const void* q, CgState* st,
                                                  const double* in, int nfold, int it, double* partials, size_t n) {
   using T = typename IO<P>::T;
-  if (st->done) return;
+  if (nfold ? group_flag(&st->done) : st->done != 0) return;
   double alpha = 0.0;
   if (nfold) {
     if (!cg_alpha_of(st, in, nfold, 1, it, blockIdx.x == 0 && threadIdx.x == 0, alpha)) return;

@@ -423,9 +423,10 @@ __device__ inline float2 coarse_row(const MgGeom& m, const float2* M, X x, size_
 
 // The scalars of one coarse BiCGStab, on the device. The kernels of an
 // iteration add the partial sums they need themselves, each workgroup for
-// itself and all in the same order, so an iteration has no host round trip; workgroup 0 writes what later launches read. done may be set
-// while other workgroups of the same launch look at it: what they would still
-// write is not read any more.
+// itself and all in the same order, so an iteration has no host round trip;
+// workgroup 0 writes what later launches read. done may be set while other
+// workgroups of the same launch look at it, each once (group_flag): what they would
+// still write is not read any more.
 struct CoarseState {
   double rho[2][2];  // of even and odd iterations
   double alpha[2], omega[2];
@@ -433,12 +434,10 @@ struct CoarseState {
   int done, iters;
 };
 
-__device__ inline bool cs_done(const CoarseState* st) {
-  return __hip_atomic_load(&st->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-}
+__device__ inline bool cs_done(const CoarseState* st) { return group_flag(&st->done); }
 __device__ inline void cs_stop(CoarseState* st, int iters) {
   st->iters = iters;
-  __hip_atomic_store(&st->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  set_flag(&st->done);
 }
 __device__ inline float2 fmulc(float2 s, float2 v) { return make_float2(s.x * v.x - s.y * v.y, s.x * v.y + s.y * v.x); }
 __device__ inline float2 fadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }

@@ -244,7 +244,7 @@ template <int P>
 __global__ void __launch_bounds__(SBS) k_stag_r(void* r, const void* q, CgState* st, const double* in, int nfold, int it,
                                                 double* out, size_t vh) {
   using T = typename SIO<P>::T;
-  if (st->done) return;
+  if (nfold ? group_flag(&st->done) : st->done != 0) return;
   double alpha = 0.0;
   if (nfold) {
     if (!cg_alpha_of(st, in, nfold, 0, it, blockIdx.x == 0 && threadIdx.x == 0, alpha)) return;
