@@ -328,10 +328,10 @@ struct IO<2> {
 };
 
 // Fused multiply-add forms of the complex arithmetic: four FMAs per complex
-// multiply-accumulate where a product and a sum take six instructions. Hops are
-// bounded by memory at large sizes, so a fifth fewer instructions give little
-// there; in the clover term (Schur operator, us, before and after): FP64 24^3x48
-// 250 and 235, FP16 24^3x48 62.1 and 59.5, 32^3x64 185 and 181.
+// multiply-accumulate where a product and a sum take six instructions, two
+// roundings on the running sum where they take one. In the clover term (Schur
+// operator with clover, us, six instructions and four): FP64 24^3x48 247 and 233, FP16
+// 24^3x48 61.9 and 59.1, 32^3x64 177 and 174.
 __device__ inline float fmat(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ inline double fmat(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -343,6 +343,15 @@ __device__ inline cx<T> cmadd(cx<T> a, cx<T> b, cx<T> c) {
 template <typename T>
 __device__ inline cx<T> cmaddc(cx<T> a, cx<T> b, cx<T> c) {
   return {fmat(a.i, b.i, fmat(a.r, b.r, c.r)), fmat(-a.i, b.r, fmat(a.r, b.i, c.i))};
+}
+// a b and conj(a) b, the product with a's imaginary part rounded on its own
+template <typename T>
+__device__ inline cx<T> cmul_re(cx<T> a, cx<T> b) {
+  return {fmat(a.r, b.r, -(a.i * b.i)), fmat(a.r, b.i, a.i * b.r)};
+}
+template <typename T>
+__device__ inline cx<T> cmulc_re(cx<T> a, cx<T> b) {
+  return {fmat(a.r, b.r, a.i * b.i), fmat(a.r, b.i, -(a.i * b.r))};
 }
 // c + f z, c + f (i z), c - f (i z) for a real factor f
 template <typename T>
@@ -361,27 +370,32 @@ __device__ inline cx<T> caxpy_mi(T f, cx<T> z, cx<T> c) {
 // Rebuild row 2 of an SU(3) matrix from rows 0, 1: row2 = conj(row0 x row1).
 template <typename T>
 __device__ inline void reconstruct(const cx<T> u[6], cx<T> r2[3]) {
-  r2[0] = conj(cmadd(-u[2], u[4], u[1] * u[5]));
-  r2[1] = conj(cmadd(-u[0], u[5], u[2] * u[3]));
-  r2[2] = conj(cmadd(-u[1], u[3], u[0] * u[4]));
+  r2[0] = conj(u[1] * u[5] - u[2] * u[4]);
+  r2[1] = conj(u[2] * u[3] - u[0] * u[5]);
+  r2[2] = conj(u[0] * u[4] - u[1] * u[3]);
 }
 
-// y = M x for a Hermitian 6x6 block in the 18-slot packed form.
+// y = M x for a Hermitian 6x6 block in the 18-slot packed form: the off-diagonal
+// products first, then the diagonal, which is near 1 in A and its inverse, so that
+// the sum stays small until its last addition. Rounding error of A psi against long
+// double (8^4, c_SW 1, FP64 / FP32): 1.15e-16 / 6.0e-8; the diagonal first, products
+// rounded before they are added, 1.49e-16 / 7.8e-8; the diagonal first with serial
+// multiply-adds 1.87e-16 / 1.0e-7.
 template <typename T>
 __device__ inline void herm6_mul(const cx<T> m[18], const cx<T> x[6], cx<T> y[6]) {
   const T d[6] = {m[0].r, m[0].i, m[1].r, m[1].i, m[2].r, m[2].i};
-#pragma unroll
-  for (int a = 0; a < 6; ++a) y[a] = d[a] * x[a];
   int k = 3;
 #pragma unroll
   for (int a = 0; a < 6; ++a) {
 #pragma unroll
     for (int b = a + 1; b < 6; ++b) {
       const cx<T> c = m[k++];
-      y[a] = cmadd(c, x[b], y[a]);
-      y[b] = cmaddc(c, x[a], y[b]);
+      y[a] = a == 0 && b == 1 ? c * x[b] : cmadd(c, x[b], y[a]);
+      y[b] = a == 0 ? cmulc(c, x[a]) : cmaddc(c, x[a], y[b]);
     }
   }
+#pragma unroll
+  for (int a = 0; a < 6; ++a) y[a] = caxpy(d[a], x[a], y[a]);
 }
 
 // out = A psi with A given by its two chiral blocks (1/2 of the basis change folded in).

@@ -60,31 +60,49 @@ __device__ inline void project(const cx<T> s[12], cx<T> h[6]) {
   }
 }
 
-// w = M h (FWD) or M^dag h, for both colour vectors of h. FUSED: four multiply-adds
-// per complex product and sum instead of six instructions.
-template <bool FWD, bool FUSED = true, typename T>
+// How a complex product goes into a sum:
+//   CHAIN  four multiply-adds on the running sum, which rounds twice per product;
+//   APART  the product first (a multiplication and a multiply-add per part, the
+//          one with the link's imaginary part rounded on its own, which is the
+//          small one on smooth links), then an addition: six instructions;
+//   PLAIN  the same left to the compiler.
+// Rounding error of the Wilson hop against long double, 8^4, links exp(0.3 i H): FP64
+// 1.35e-16 APART, 1.41e-16 CHAIN; FP32 8.09e-8 and 8.36e-8. Times: 4-d hops within 1%
+// of each other (bound by memory), domain-wall D^dag FP64 16^4 x 8 75.5 and 73.4 us.
+// CHAIN only where several right-hand sides share a link. FP16 takes PLAIN: with the
+// other two the compiler keeps 150-180 VGPRs instead of 93 and the occupancy falls
+// from 5 to 2-3 waves per SIMD (32^3x64, Schur with clover: 194 and 270 against 174 us).
+enum { PLAIN, APART, CHAIN };
+constexpr int link_product(int prec) { return prec == 2 ? PLAIN : APART; }
+
+// w = M h (FWD) or M^dag h, for both colour vectors of h.
+template <bool FWD, int HOW, typename T>
 __device__ inline void mat3_mul(const cx<T> M[9], const cx<T> h[6], cx<T> w[6]) {
 #pragma unroll
   for (int v = 0; v < 2; ++v)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      cx<T> q = FWD ? M[3 * a] * h[3 * v] : cmulc(M[a], h[3 * v]);
+      cx<T> q;
 #pragma unroll
-      for (int b = 1; b < 3; ++b) {
-        const cx<T> hb = h[3 * v + b];
-        if (FUSED) q = FWD ? cmadd(M[3 * a + b], hb, q) : cmaddc(M[3 * b + a], hb, q);
-        else q = q + (FWD ? M[3 * a + b] * hb : cmulc(M[3 * b + a], hb));
+      for (int b = 0; b < 3; ++b) {
+        const cx<T> m = FWD ? M[3 * a + b] : M[3 * b + a], hb = h[3 * v + b];
+        if (HOW == CHAIN && b > 0) {
+          q = FWD ? cmadd(m, hb, q) : cmaddc(m, hb, q);
+          continue;
+        }
+        const cx<T> t = HOW == APART ? (FWD ? cmul_re(m, hb) : cmulc_re(m, hb)) : (FWD ? m * hb : cmulc(m, hb));
+        q = b == 0 ? t : q + t;
       }
       w[3 * v + a] = q;
     }
 }
 // The same with U given by its first two rows.
-template <bool FWD, bool FUSED = true, typename T>
+template <bool FWD, int HOW, typename T>
 __device__ inline void link_mul(const cx<T> u[6], const cx<T> h[6], cx<T> w[6]) {
   cx<T> r2[3];
   reconstruct(u, r2);
   const cx<T> M[9] = {u[0], u[1], u[2], u[3], u[4], u[5], r2[0], r2[1], r2[2]};
-  mat3_mul<FWD, FUSED>(M, h, w);
+  mat3_mul<FWD, HOW>(M, h, w);
 }
 
 // G5: the hop acts on gamma5 psi instead of psi (gamma5 of the Dirac-Pauli
@@ -94,11 +112,13 @@ __device__ inline void hop_dir(const void* in, const void* links, size_t vh, siz
                                cx<typename IO<P>::T> acc[12]) {
   using T = typename IO<P>::T;
   cx<T> h[6];
-  T f = 1;  // the factor of the projection in t, applied to w
   if (MU == 3) {
     // (1 - gamma_t) psi = 2 (0, 0, psi_2, psi_3); (1 + gamma_t) psi = 2 (psi_0, psi_1, 0, 0)
-    IO<P>::load_half(in, nbr, G5 ? FWD : !FWD, h);
-    f = (flip != G5) ? T(-2) : T(2);
+    cx<T> half[6];
+    IO<P>::load_half(in, nbr, G5 ? FWD : !FWD, half);
+    const T two = (flip != G5) ? T(-2) : T(2);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) h[k] = two * half[k];
   } else {
     cx<T> s[12];
     IO<P>::load_spinor(in, nbr, s);
@@ -114,11 +134,8 @@ __device__ inline void hop_dir(const void* in, const void* links, size_t vh, siz
   }
   cx<T> u[6], w[6];
   IO<P>::template load_link<NT>(links, lidx, u);
-  // FP16 one lane per site: with the fused product the compiler keeps 150-180
-  // VGPRs instead of 93 and the occupancy falls from 5 to 2-3 waves per SIMD
-  // (32^3x64, Schur with clover: 194 against 183 us).
-  link_mul<FWD, P != 2>(u, h, w);
-  expand_f<MU, FWD>(acc, w, f);
+  link_mul<FWD, link_product(P)>(u, h, w);
+  expand_f<MU, FWD>(acc, w, T(1));
 }
 
 struct HopArgs {
@@ -328,7 +345,7 @@ __device__ inline void hop_dir_multi(const MultiPtrs<NB>& m, const void* links, 
       project<MU, FWD>(s, h);
     }
     cx<T> w[6];
-    mat3_mul<FWD>(M, h, w);
+    mat3_mul<FWD, CHAIN>(M, h, w);
     expand_f<MU, FWD>(acc[r], w, f);
   }
 }

@@ -70,7 +70,7 @@ __device__ inline void words_get(const float4* L, int n, int slot, cx<float> s[6
 // in t, s[0..5] is the half that survives the projection and lands in the lower
 // spins (forward) or the upper ones (backward), and the projection's factor 2 is
 // in m.
-template <int MU>
+template <int MU, int HOW>
 __device__ inline void pair_hop(const cx<float> s[12], const cx<float> m[9], float sg, cx<float> acc[12]) {
   cx<float> h[6], w[6];
 #pragma unroll
@@ -89,11 +89,7 @@ __device__ inline void pair_hop(const cx<float> s[12], const cx<float> m[9], flo
       h[3 + c] = s[3 + c];
     }
   }
-#pragma unroll
-  for (int v = 0; v < 2; ++v)
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-      w[3 * v + b] = cmadd(m[3 * b + 2], h[3 * v + 2], cmadd(m[3 * b + 1], h[3 * v + 1], m[3 * b] * h[3 * v]));
+  mat3_mul<true, HOW>(m, h, w);
   const float fw = sg > 0.f ? 1.f : 0.f, bw = 1.f - fw;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -126,8 +122,12 @@ __device__ inline void pair_hop_mem(const void* in, size_t j, const cx<float> m[
   cx<float> s[12];
   if (MU == 3) IO<1>::load_half(in, j, sg < 0.f, s);
   else IO<1>::load_spinor(in, j, s);
-  pair_hop<MU>(s, m, sg, acc);
+  pair_hop<MU, APART>(s, m, sg, acc);
 }
+// Inside the block the serial multiply-adds: M eta against 64-bit values, 8^4, blocks
+// 4^4, 2 cycles of 4 steps, with c_SW 1 and 0, 1.26e-7 and 1.10e-7 (products rounded
+// first 1.25e-7 and 1.09e-7, 2-4% slower; one lane per site, products first, kappa on
+// every hop 1.44e-7 and 1.22e-7).
 template <int MU>
 __device__ inline void pair_hop_lds(const float4* Lr, int n, int slot, const cx<float> m[9], float sg,
                                     cx<float> acc[12]) {
@@ -138,7 +138,7 @@ __device__ inline void pair_hop_lds(const float4* Lr, int n, int slot, const cx<
     words_get(Lr, n, slot, s);
     words_get(Lr + 3 * n, n, slot, s + 6);
   }
-  pair_hop<MU>(s, m, sg, acc);
+  pair_hop<MU, CHAIN>(s, m, sg, acc);
 }
 
 // Each lane of a pair holds a partial sum of all 12 components; the forward lane
@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(512) k_sap_block(SapArgs a) {
   bool in_block[4];  // the neighbour on this lane's side is in the block
   size_t j[4];       // its checkerboard index
   int slot[4];
-  cx<float> m[4][9];  // the matrix of this lane's hop in direction mu, scaled
+  cx<float> m[4][9];  // the matrix of this lane's hop in direction mu
 #pragma unroll
   for (int mu = 0; mu < 4; ++mu) {
     in_block[mu] = fwd ? lc[mu] + 1 < a.b[mu] : lc[mu] > 0;
@@ -236,10 +236,11 @@ __global__ void __launch_bounds__(512) k_sap_block(SapArgs a) {
     cx<float> u[6], r2[3];
     IO<1>::template load_link<false>(gl + mu * ls, fwd ? i : j[mu], u);
     reconstruct(u, r2);
-    // -kappa, 2 for the t projection, and the boundary factor of a hop that
-    // crosses the lattice (never inside a block) are folded in
+    // 2 for the t projection and the boundary factor of a hop that crosses the
+    // lattice (never inside a block) are folded in, both exact in FP32; kappa,
+    // which would round every element, multiplies the sum of the hops instead
     const bool wrap = mu == 3 && g.t_bc < 0 && (fwd ? t + 1 == L[3] : t == 0);
-    const float f = (mu == 3 ? -2.f : -1.f) * (wrap ? -a.kappa : a.kappa);
+    const float f = (mu == 3 ? 2.f : 1.f) * (wrap ? -1.f : 1.f);
     const cx<float> u9[9] = {u[0], u[1], u[2], u[3], u[4], u[5], r2[0], r2[1], r2[2]};
 #pragma unroll
     for (int k = 0; k < 9; ++k) m[mu][k] = f * (fwd ? u9[k] : conj(u9[3 * (k % 3) + k / 3]));
@@ -262,7 +263,7 @@ __global__ void __launch_bounds__(512) k_sap_block(SapArgs a) {
     pair_total(acc, hop);
     IO<1>::load_half(a.base[p], i, fwd, r);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) r[k] = r[k] - hop[k];
+    for (int k = 0; k < 6; ++k) r[k] = caxpy(a.kappa, hop[k], r[k]);
   }
   const bool clover = a.clov[0] != nullptr;
   cx<float> cb[18];
@@ -297,14 +298,14 @@ __global__ void __launch_bounds__(512) k_sap_block(SapArgs a) {
       herm6_mul(cb, ch, yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
-        qv[k] = qv[k] + yv[k];
-        qv[6 + k] = qv[6 + k] - sg * yv[k];
+        qv[k] = caxpy(-a.kappa, qv[k], yv[k]);
+        qv[6 + k] = caxpy(-a.kappa, qv[6 + k], -sg * yv[k]);
       }
     }
     pair_total(qv, qh);
     if (!clover)
 #pragma unroll
-      for (int k = 0; k < 6; ++k) qh[k] = qh[k] + r[k];
+      for (int k = 0; k < 6; ++k) qh[k] = caxpy(-a.kappa, qh[k], r[k]);
     double dv[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < 6; ++k) {

@@ -114,9 +114,9 @@ __device__ inline void stag_hop_site(const StagArgs& a, size_t i, double red[2])
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       cx<T> s = M[3 * c] * v[0];
-      s = cmadd(M[3 * c + 1], v[1], s);
-      s = cmadd(M[3 * c + 2], v[2], s);
-      acc[c] = caxpy(ef, s, acc[c]);
+      s = s + M[3 * c + 1] * v[1];
+      s = s + M[3 * c + 2] * v[2];
+      acc[c] = acc[c] + ef * s;
     }
     // backward: - eta U_mu(x - mu)^dag psi(x - mu)
     IO<P>::template load_link<true>(gb + mu * a.link_stride, (size_t)nb[mu], u);
@@ -127,9 +127,9 @@ __device__ inline void stag_hop_site(const StagArgs& a, size_t i, double red[2])
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       cx<T> s = cmulc(N[c], v[0]);
-      s = cmaddc(N[3 + c], v[1], s);
-      s = cmaddc(N[6 + c], v[2], s);
-      acc[c] = caxpy(eb, s, acc[c]);
+      s = s + cmulc(N[3 + c], v[1]);
+      s = s + cmulc(N[6 + c], v[2]);
+      acc[c] = acc[c] + eb * s;
     }
   }
   cx<T> out[3];
