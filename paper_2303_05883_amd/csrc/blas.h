@@ -37,7 +37,8 @@ struct Fold {
 // Whether n records are folded: up to 1536 (36 KB from L2 per workgroup and
 // about 1.5 us) that is cheaper than a one-block launch (about 4 us and the gap
 // before the next one); beyond, the reads of all workgroups add up.
-inline bool fold_ok(int n) { return n <= 1536; }
+constexpr int FOLD_MAX = 1536;
+inline bool fold_ok(int n) { return n <= FOLD_MAX; }
 
 int blas_blocks(size_t vh);
 int blas_p_update(lqcd_ctx* c, int prec, const void* r, void* p, const void* v, Scal* sc, Fold f = Fold());

@@ -421,15 +421,18 @@ __device__ inline float2 coarse_row(const MgGeom& m, const float2* M, X x, size_
   return make_float2(re, im);
 }
 
-// The scalars of one coarse BiCGStab, on the device. The kernels of an
-// iteration add the partial sums they need themselves, each workgroup for
-// itself and all in the same order, so an iteration has no host round trip;
+// The scalars of one coarse BiCGStab, on the device, so an iteration has no host
+// round trip. The kernels of an iteration add the partial sums they need themselves,
+// each workgroup for itself and all in the same order, where records and workgroups
+// are few (coarse_fold), else a one-block kernel has added them (np = 0 below);
 // workgroup 0 writes what later launches read. done may be set while other
 // workgroups of the same launch look at it, each once (group_flag): what they would
 // still write is not read any more.
 struct CoarseState {
   double rho[2][2];  // of even and odd iterations
   double alpha[2], omega[2];
+  float2 p_r[2];     // beta, -beta omega
+  float2 s_v;        // -alpha
   double target2;
   int done, iters;
 };
@@ -504,6 +507,11 @@ __global__ void __launch_bounds__(256) k_c_start(const float2* b, float2* x, flo
 // the convergence test (true: stop); p = r + b p + c v with b = beta, c = -beta omega
 __device__ inline bool cs_beta(const double* partials, int np, CoarseState* st, int it, int max_iters, double tol2,
                                float2& b, float2& c) {
+  if (np == 0) {
+    b = st->p_r[0];
+    c = st->p_r[1];
+    return false;
+  }
   double s[3];
   sum_partials<3>(partials, np, s);
   const cx<double> rho = {s[0], s[1]};
@@ -532,6 +540,10 @@ __device__ inline bool cs_beta(const double* partials, int np, CoarseState* st, 
 
 // alpha = rho / <rhat, v> from the np records of the latter; a = -alpha (true: stop)
 __device__ inline bool cs_alpha(const double* partials, int np, CoarseState* st, int it, float2& a) {
+  if (np == 0) {
+    a = st->s_v;
+    return false;
+  }
   double d[2];
   sum_partials<2>(partials, np, d);
   const bool stop = d[0] == 0.0 && d[1] == 0.0;
@@ -544,6 +556,42 @@ __device__ inline bool cs_alpha(const double* partials, int np, CoarseState* st,
   }
   a = make_float2((float)-ar, (float)-ai);
   return stop;
+}
+
+// omega = <t, s> / <t, t> from the np records of <s, t>, <t, t>
+__device__ inline cx<double> cs_omega(const double* partials, int np, CoarseState* st) {
+  if (np == 0) return {st->omega[0], st->omega[1]};
+  double d[3];
+  sum_partials<3>(partials, np, d);
+  const cx<double> w = d[2] != 0.0 ? cx<double>{d[0] / d[2], -d[1] / d[2]} : cx<double>{0.0, 0.0};
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->omega[0] = w.r;
+    st->omega[1] = w.i;
+  }
+  return w;
+}
+
+// The same as one-block kernels
+constexpr int CFIN = 1024;
+__global__ void __launch_bounds__(CFIN) k_c_beta(const double* partials, int np, CoarseState* st, int it, int max_iters,
+                                                 double tol2) {
+  if (cs_done(st)) return;
+  float2 b, c;
+  cs_beta(partials, np, st, it, max_iters, tol2, b, c);
+  if (threadIdx.x == 0) {
+    st->p_r[0] = b;
+    st->p_r[1] = c;
+  }
+}
+__global__ void __launch_bounds__(CFIN) k_c_alpha(const double* partials, int np, CoarseState* st, int it) {
+  if (cs_done(st)) return;
+  float2 a;
+  cs_alpha(partials, np, st, it, a);
+  if (threadIdx.x == 0) st->s_v = a;
+}
+__global__ void __launch_bounds__(CFIN) k_c_omega(const double* partials, int np, CoarseState* st) {
+  if (cs_done(st)) return;
+  cs_omega(partials, np, st);
 }
 
 __device__ inline float4 pair_fma(float2 f, float4 v, float4 s) {
@@ -612,20 +660,13 @@ __global__ void __launch_bounds__(256) k_c_st(MgGeom m, const float2* M, const f
   capply_body<SUB, 2>(m, M, x, t, nullptr, pout);
 }
 
-// omega = <t, s> / <t, t> from the np2 records of <s, t>, <t, t>; x += alpha p +
-// omega s, r = s - omega t, partial sums of <rhat, r> and |r|^2
+// omega; x += alpha p + omega s, r = s - omega t, partial sums of <rhat, r> and |r|^2
 __global__ void __launch_bounds__(256) k_c_xr(float2* x, const float2* p, const float2* s, const float2* t, float2* r,
                                               const float2* rh, const double* partials2, int np2, double* partials,
                                               CoarseState* st, size_t n) {
   if (cs_done(st)) return;
-  double d[3];
-  sum_partials<3>(partials2, np2, d);
-  const double wr = d[2] != 0.0 ? d[0] / d[2] : 0.0, wi = d[2] != 0.0 ? -d[1] / d[2] : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->omega[0] = wr;
-    st->omega[1] = wi;
-  }
-  const float2 al = make_float2((float)st->alpha[0], (float)st->alpha[1]), om = make_float2((float)wr, (float)wi);
+  const cx<double> w = cs_omega(partials2, np2, st);
+  const float2 al = make_float2((float)st->alpha[0], (float)st->alpha[1]), om = make_float2((float)w.r, (float)w.i);
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   double e[3] = {0.0, 0.0, 0.0};
   if (i < n) {
@@ -724,6 +765,13 @@ int prolong_to(lqcd_ctx* c, MgState& s, const float2* e, void* x2) {
 int capply_sub(const MgState& s) { return s.nc() * 16 <= (size_t)2048 * 256 ? 16 : 4; }
 int capply_blocks(const MgState& s) { return grid1(s.nc() * capply_sub(s)); }
 
+// n if the n records of a launch are added by each of the `readers` workgroups of the
+// next, 0 if by a one-block kernel. The redundant reads grow as the square of the
+// rows, so they are held to those of fold_ok's bound. Microseconds per coarse
+// iteration, folded and not: 8192 rows 22.6 and 27.3, 32768 54.4 and 60.2, 196608 (the
+// border) 191 and 198, 393216 655 and 641, 1048576 452 and 358.
+int coarse_fold(int n, int readers) { return (size_t)n * readers <= (size_t)FOLD_MAX * FOLD_MAX ? n : 0; }
+
 template <int DOT>
 int capply(lqcd_ctx* c, MgState& s, const float2* x, float2* y, const float2* w = nullptr, double* partials = nullptr) {
   const dim3 grid(capply_blocks(s));
@@ -752,16 +800,19 @@ int coarse_solve(lqcd_ctx* c, MgState& s, int& iters) {
   const int nv = grid1(n), na = capply_blocks(s), most = s.prm.coarse_max_iter;
   const bool one = capply_sub(s) == 16;  // vector updates inside the operator's launches
   const double tol2 = s.prm.coarse_tol * s.prm.coarse_tol;
+  // records that the next launch adds itself, or 0: the sums of beta, alpha, omega
+  const int fb = coarse_fold(nv, one ? na : nv), fa = coarse_fold(na, one ? na : nv), fo = coarse_fold(na, nv);
   hipStream_t st = c->stream;
   // p and v = D_c p of iteration it
   auto direction = [&](int it) -> int {
     const int w = it & 1;
+    if (!fb) hipLaunchKernelGGL(k_c_beta, dim3(1), dim3(CFIN), 0, st, s.partials[2], nv, s.cs, it, most, tol2);
     if (one) {
       hipLaunchKernelGGL(k_c_pv<16>, dim3(na), block, 0, st, s.m, s.M, r, p[1 - w], v[1 - w], p[w], v[w], rh,
-                         s.partials[2], nv, s.partials[0], s.cs, it, most, tol2);
+                         s.partials[2], fb, s.partials[0], s.cs, it, most, tol2);
       return LQCD_OK;
     }
-    hipLaunchKernelGGL(k_c_p, grid, block, 0, st, r, p[1 - w], v[1 - w], p[w], s.partials[2], nv, s.cs, it, most, tol2,
+    hipLaunchKernelGGL(k_c_p, grid, block, 0, st, r, p[1 - w], v[1 - w], p[w], s.partials[2], fb, s.cs, it, most, tol2,
                        n);
     return capply<1>(c, s, p[w], v[w], rh, s.partials[0]);
   };
@@ -770,14 +821,16 @@ int coarse_solve(lqcd_ctx* c, MgState& s, int& iters) {
   volatile int* done = reinterpret_cast<int*>(c->hscal + 40);  // pinned: done, iters
   for (int it = 0, chunk = s.coarse_last;; chunk = 2) {
     for (int k = 0; k < chunk; ++k, ++it) {
+      if (!fa) hipLaunchKernelGGL(k_c_alpha, dim3(1), dim3(CFIN), 0, st, s.partials[0], na, s.cs, it);
       if (one) {
-        hipLaunchKernelGGL(k_c_st<16>, dim3(na), block, 0, st, s.m, s.M, r, v[it & 1], q, t, s.partials[0], na,
+        hipLaunchKernelGGL(k_c_st<16>, dim3(na), block, 0, st, s.m, s.M, r, v[it & 1], q, t, s.partials[0], fa,
                            s.partials[1], s.cs, it);
       } else {
-        hipLaunchKernelGGL(k_c_s, grid, block, 0, st, r, v[it & 1], q, s.partials[0], na, s.cs, it, n);
+        hipLaunchKernelGGL(k_c_s, grid, block, 0, st, r, v[it & 1], q, s.partials[0], fa, s.cs, it, n);
         LQ_TRY(capply<2>(c, s, q, t, nullptr, s.partials[1]));
       }
-      hipLaunchKernelGGL(k_c_xr, grid, block, 0, st, x, p[it & 1], q, t, r, rh, s.partials[1], na, s.partials[2], s.cs,
+      if (!fo) hipLaunchKernelGGL(k_c_omega, dim3(1), dim3(CFIN), 0, st, s.partials[1], na, s.cs);
+      hipLaunchKernelGGL(k_c_xr, grid, block, 0, st, x, p[it & 1], q, t, r, rh, s.partials[1], fo, s.partials[2], s.cs,
                          n);
       LQ_TRY(direction(it + 1));
     }
