@@ -69,24 +69,24 @@ static void dfree(void*& p) {
   p = nullptr;
 }
 
+// takes block k out of the pool
+static Block pool_take(lqcd_ctx* c, int k) {
+  const Block b = c->pool[k];
+  for (--c->pool_n; k < c->pool_n; ++k) c->pool[k] = c->pool[k + 1];
+  c->pool_bytes -= b.bytes;
+  return b;
+}
+
 void pool_release(lqcd_ctx* c, size_t keep) {
-  size_t n = 0;
-  for (; n < c->pool.size() && c->pool_bytes > keep; ++n) {
-    (void)hipFree(c->pool[n].first);
-    c->pool_bytes -= c->pool[n].second;
-  }
-  c->pool.erase(c->pool.begin(), c->pool.begin() + n);
+  while (c->pool_n > 0 && c->pool_bytes > keep) (void)hipFree(pool_take(c, 0).p);
 }
 
 int Scratch::get(size_t bytes, void** p, const char* what) {
-  auto& pool = c_->pool;
-  mem_.reserve(mem_.size() + 1);
-  for (size_t k = pool.size(); k-- > 0;)
-    if (pool[k].second == bytes) {
-      *p = pool[k].first;
-      pool.erase(pool.begin() + k);
-      c_->pool_bytes -= bytes;
-      mem_.emplace_back(*p, bytes);
+  if (n_ == POOL_BLOCKS) return set_error(LQCD_ENOMEM, what);
+  for (int k = c_->pool_n; k-- > 0;)
+    if (c_->pool[k].bytes == bytes) {
+      mem_[n_++] = pool_take(c_, k);
+      *p = mem_[n_ - 1].p;
       return LQCD_OK;
     }
   if (hipMalloc(p, bytes) != hipSuccess) {
@@ -98,19 +98,21 @@ int Scratch::get(size_t bytes, void** p, const char* what) {
       return set_error(LQCD_ENOMEM, what);
     }
   }
-  mem_.emplace_back(*p, bytes);
+  mem_[n_++] = {*p, bytes};
   return LQCD_OK;
 }
 
 Scratch::~Scratch() {
-  for (auto& m : mem_) {
-    if (m.second > POOL_MAX) {
-      (void)hipFree(m.first);
+  for (int k = 0; k < n_; ++k) {
+    const Block& m = mem_[k];
+    if (m.bytes > POOL_MAX) {
+      (void)hipFree(m.p);
       continue;
     }
-    pool_release(c_, POOL_MAX - m.second);
-    c_->pool.push_back(m);
-    c_->pool_bytes += m.second;
+    pool_release(c_, POOL_MAX - m.bytes);
+    if (c_->pool_n == POOL_BLOCKS) (void)hipFree(pool_take(c_, 0).p);
+    c_->pool[c_->pool_n++] = m;
+    c_->pool_bytes += m.bytes;
   }
 }
 

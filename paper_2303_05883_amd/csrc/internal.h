@@ -37,7 +37,6 @@
 #include <cstdint>
 #include <cstdlib>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "../../include/lqcd.h"
@@ -108,6 +107,14 @@ struct Workspace;    // solver vectors, allocated on first use (solver.hip)
 
 }  // namespace lq
 
+namespace lq {
+struct Block {
+  void* p;
+  size_t bytes;
+};
+constexpr int POOL_BLOCKS = 64;  // idle per context, and held by one call's Scratch (at most 19 are used)
+}  // namespace lq
+
 struct lqcd_ctx {
   lq::Geom g;
   hipStream_t stream = nullptr;
@@ -157,7 +164,8 @@ struct lqcd_ctx {
   void* sap_res = nullptr;
   void* sap_delta = nullptr;
   // device blocks of finished calls kept for the next ones (lq::Scratch)
-  std::vector<std::pair<void*, size_t>> pool;
+  lq::Block pool[lq::POOL_BLOCKS];
+  int pool_n = 0;
   size_t pool_bytes = 0;
 };
 
@@ -168,7 +176,8 @@ int set_error(int status, const std::string& msg);
 
 // Device blocks of one call, given back to the context's pool at its end. The pool
 // is bounded by POOL_MAX (oldest blocks freed first), emptied when an allocation
-// fails and freed with the context. A context's calls run on its one stream and are
+// fails and freed with the context; it is of a fixed size, so that it throws nothing
+// into a C caller. A context's calls run on its one stream and are
 // made by one thread at a time, so a block's last use lies before its next. Contents
 // are what the last call left. hipMalloc and hipFree (which waits for the device and
 // unmaps) of a solve's vectors on each call, against blocks kept: domain-wall FP32
@@ -185,7 +194,8 @@ class Scratch {
 
  private:
   lqcd_ctx* c_;
-  std::vector<std::pair<void*, size_t>> mem_;
+  Block mem_[POOL_BLOCKS];
+  int n_ = 0;
 };
 void pool_release(lqcd_ctx* c, size_t keep = 0);  // down to keep bytes
 #define LQ_HIP(call)                                                                    \
