@@ -54,14 +54,62 @@ int set_error(int status, const std::string& msg) {
   return status;
 }
 
-static int dalloc(void** p, size_t bytes) {
-  if (*p) return LQCD_OK;
-  if (hipMalloc(p, bytes) != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
-    return set_error(LQCD_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+// Idle device blocks of all contexts, the one idle longest first
+struct Idle {
+  Block b;
+  const lqcd_ctx* owner;  // its stream orders the block's next use after the last
+};
+static std::mutex g_idle_mutex;
+static Idle g_idle[IDLE_BLOCKS];
+static int g_idle_n = 0;
+static size_t g_idle_bytes = 0;
+
+// takes the first (newest: last) idle block that fits out of the list (with the lock held)
+template <typename F>
+static bool idle_take(Block* b, bool newest, F&& fits) {
+  for (int n = 0; n < g_idle_n; ++n) {
+    int k = newest ? g_idle_n - 1 - n : n;
+    if (!fits(g_idle[k])) continue;
+    *b = g_idle[k].b;
+    for (--g_idle_n; k < g_idle_n; ++k) g_idle[k] = g_idle[k + 1];
+    g_idle_bytes -= b->bytes;
+    return true;
   }
-  return LQCD_OK;
+  return false;
+}
+
+// frees the idle blocks that fit, outside the lock (hipFree waits for the device,
+// and so for their last use on whatever stream); whether there were any
+template <typename F>
+static bool idle_free(F&& fits) {
+  for (bool any = false;; any = true) {
+    Block b;
+    {
+      std::lock_guard<std::mutex> lock(g_idle_mutex);
+      if (!idle_take(&b, false, fits)) return any;
+    }
+    (void)hipFree(b.p);
+  }
+}
+
+void idle_release(const lqcd_ctx* c) {
+  idle_free([c](const Idle& i) { return i.owner == c; });
+}
+
+int device_alloc(void** p, size_t bytes, const char* what) {
+  if (hipMalloc(p, bytes) == hipSuccess) return LQCD_OK;
+  (void)hipGetLastError();
+  int dev = -1;
+  (void)hipGetDevice(&dev);
+  if (idle_free([dev](const Idle& i) { return i.owner->device == dev; }) && hipMalloc(p, bytes) == hipSuccess)
+    return LQCD_OK;
+  (void)hipGetLastError();
+  *p = nullptr;
+  return set_error(LQCD_ENOMEM, std::string(what) + " (" + std::to_string(bytes) + " bytes)");
+}
+
+static int dalloc(void** p, size_t bytes) {
+  return *p ? LQCD_OK : device_alloc(p, bytes, "device allocation failed");
 }
 
 static void dfree(void*& p) {
@@ -69,50 +117,38 @@ static void dfree(void*& p) {
   p = nullptr;
 }
 
-// takes block k out of the pool
-static Block pool_take(lqcd_ctx* c, int k) {
-  const Block b = c->pool[k];
-  for (--c->pool_n; k < c->pool_n; ++k) c->pool[k] = c->pool[k + 1];
-  c->pool_bytes -= b.bytes;
-  return b;
-}
-
-void pool_release(lqcd_ctx* c, size_t keep) {
-  while (c->pool_n > 0 && c->pool_bytes > keep) (void)hipFree(pool_take(c, 0).p);
-}
-
 int Scratch::get(size_t bytes, void** p, const char* what) {
-  if (n_ == POOL_BLOCKS) return set_error(LQCD_ENOMEM, what);
-  for (int k = c_->pool_n; k-- > 0;)
-    if (c_->pool[k].bytes == bytes) {
-      mem_[n_++] = pool_take(c_, k);
-      *p = mem_[n_ - 1].p;
-      return LQCD_OK;
-    }
-  if (hipMalloc(p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    pool_release(c_);
-    if (hipMalloc(p, bytes) != hipSuccess) {
-      *p = nullptr;
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, what);
-    }
+  if (n_ == SCRATCH_BLOCKS) return set_error(LQCD_ENOMEM, what);
+  bool kept;
+  {
+    std::lock_guard<std::mutex> lock(g_idle_mutex);
+    kept = idle_take(&mem_[n_], true, [&](const Idle& i) { return i.owner == c_ && i.b.bytes == bytes; });
   }
-  mem_[n_++] = {*p, bytes};
+  if (!kept) {
+    mem_[n_].bytes = bytes;
+    LQ_TRY(device_alloc(&mem_[n_].p, bytes, what));
+  }
+  *p = mem_[n_++].p;
   return LQCD_OK;
 }
 
 Scratch::~Scratch() {
   for (int k = 0; k < n_; ++k) {
-    const Block& m = mem_[k];
-    if (m.bytes > POOL_MAX) {
-      (void)hipFree(m.p);
-      continue;
+    const Block b = mem_[k];
+    for (;;) {
+      Block old = b;  // what is to be freed: b itself if it is too large, else the oldest until there is room
+      if (b.bytes <= IDLE_MAX) {
+        std::lock_guard<std::mutex> lock(g_idle_mutex);
+        if (g_idle_n < IDLE_BLOCKS && g_idle_bytes + b.bytes <= IDLE_MAX) {
+          g_idle[g_idle_n++] = {b, c_};
+          g_idle_bytes += b.bytes;
+          break;
+        }
+        idle_take(&old, false, [](const Idle&) { return true; });
+      }
+      (void)hipFree(old.p);
+      if (old.p == b.p) break;
     }
-    pool_release(c_, POOL_MAX - m.bytes);
-    if (c_->pool_n == POOL_BLOCKS) (void)hipFree(pool_take(c_, 0).p);
-    c_->pool[c_->pool_n++] = m;
-    c_->pool_bytes += m.bytes;
   }
 }
 
@@ -278,7 +314,7 @@ int lqcd_destroy(lqcd_ctx* c) {
     dfree(c->half_c[p]);
     dfree(c->half_d[p]);
   }
-  pool_release(c);
+  idle_release(c);
   dfree(c->canon_a);
   dfree(c->canon_b);
   dfree(c->sap_res);

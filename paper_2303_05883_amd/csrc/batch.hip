@@ -170,11 +170,7 @@ struct Batch {
     if (hscal) (void)hipHostFree(hscal);
   }
   int dev_alloc(void** p, size_t bytes) {
-    if (hipMalloc(p, bytes) != hipSuccess) {
-      *p = nullptr;
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "batch workspace allocation of " + std::to_string(bytes) + " bytes failed");
-    }
+    LQ_TRY(device_alloc(p, bytes, "batch workspace allocation failed"));
     owned.push_back(*p);
     return LQCD_OK;
   }

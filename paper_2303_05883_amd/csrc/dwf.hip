@@ -1153,10 +1153,7 @@ struct DevMats {
   int upload(lqcd_ctx* c, const lqcd_dwf_params& d) {
     std::vector<double> h;
     LQ_TRY(eo_matrices(d, h));
-    if (hipMalloc(reinterpret_cast<void**>(&p), h.size() * sizeof(double)) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "domain-wall even-odd matrices");
-    }
+    LQ_TRY(device_alloc(reinterpret_cast<void**>(&p), h.size() * sizeof(double), "domain-wall even-odd matrices"));
     LQ_HIP(hipMemcpyAsync(p, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
     LQ_HIP(hipStreamSynchronize(c->stream));
     return LQCD_OK;

@@ -107,14 +107,6 @@ struct Workspace;    // solver vectors, allocated on first use (solver.hip)
 
 }  // namespace lq
 
-namespace lq {
-struct Block {
-  void* p;
-  size_t bytes;
-};
-constexpr int POOL_BLOCKS = 64;  // idle per context, and held by one call's Scratch (at most 19 are used)
-}  // namespace lq
-
 struct lqcd_ctx {
   lq::Geom g;
   hipStream_t stream = nullptr;
@@ -163,10 +155,6 @@ struct lqcd_ctx {
   // then odd half), allocated on first use
   void* sap_res = nullptr;
   void* sap_delta = nullptr;
-  // device blocks of finished calls kept for the next ones (lq::Scratch)
-  lq::Block pool[lq::POOL_BLOCKS];
-  int pool_n = 0;
-  size_t pool_bytes = 0;
 };
 
 namespace lq {
@@ -174,18 +162,30 @@ namespace lq {
 // ---------------------------------------------------------------- errors
 int set_error(int status, const std::string& msg);
 
-// Device blocks of one call, given back to the context's pool at its end. The pool
-// is bounded by POOL_MAX (oldest blocks freed first), emptied when an allocation
-// fails and freed with the context; it is of a fixed size, so that it throws nothing
-// into a C caller. A context's calls run on its one stream and are
-// made by one thread at a time, so a block's last use lies before its next. Contents
-// are what the last call left. hipMalloc and hipFree (which waits for the device and
+// hipMalloc for everything in the library. Where memory has run out, the idle blocks
+// of all contexts on this device are freed and the allocation is tried again.
+int device_alloc(void** p, size_t bytes, const char* what);
+
+struct Block {
+  void* p;
+  size_t bytes;
+};
+
+// Device blocks of one call, kept idle at its end for the context's next ones. The
+// idle blocks of all contexts together are bounded (IDLE_MAX, the ones idle longest
+// freed first), freed when any allocation of the library fails and with their
+// context. A context's calls run on its one stream and are made by one thread at a
+// time, so a block's last use lies before its next; the list of idle blocks is under
+// a lock and of a fixed size, so that nothing is thrown into a C caller. Contents are
+// what the last call left. hipMalloc and hipFree (which waits for the device and
 // unmaps) of a solve's vectors on each call, against blocks kept: domain-wall FP32
 // solve 16^4 x 8 43.1 -> 38.1 ms, 8x6x8x10 x 6 11.1 -> 9.5; SAP solve 16^3x32 33.0 -> 28.7,
 // multigrid 56.0 -> 52.2; staggered FP32 24^3x48 41.1 -> 37.9, 32^3x64 68.0 -> 64.2.
+constexpr size_t IDLE_MAX = (size_t)2 << 30;
+constexpr int IDLE_BLOCKS = 256;
+constexpr int SCRATCH_BLOCKS = 64;  // of one call at a time; at most 19 are used
 class Scratch {
  public:
-  static constexpr size_t POOL_MAX = (size_t)2 << 30;
   explicit Scratch(lqcd_ctx* c) : c_(c) {}
   Scratch(const Scratch&) = delete;
   Scratch& operator=(const Scratch&) = delete;
@@ -194,10 +194,10 @@ class Scratch {
 
  private:
   lqcd_ctx* c_;
-  Block mem_[POOL_BLOCKS];
+  Block mem_[SCRATCH_BLOCKS];
   int n_ = 0;
 };
-void pool_release(lqcd_ctx* c, size_t keep = 0);  // down to keep bytes
+void idle_release(const lqcd_ctx* c);  // frees the context's idle blocks
 #define LQ_HIP(call)                                                                    \
   do {                                                                                  \
     hipError_t e_ = (call);                                                             \

@@ -728,13 +728,7 @@ int dispatch_nc(int n, F&& f) {
   return f(std::integral_constant<int, NMAX>{});
 }
 
-int alloc(void** p, size_t bytes) {
-  if (hipMalloc(p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return set_error(LQCD_ENOMEM, "multigrid workspace allocation failed");
-  }
-  return LQCD_OK;
-}
+int alloc(void** p, size_t bytes) { return device_alloc(p, bytes, "multigrid workspace allocation failed"); }
 
 int agg_block(const MgGeom& m) { return (m.asz + 63) / 64 * 64; }
 

@@ -372,11 +372,7 @@ int sap_apply(lqcd_ctx* c, const int b[4], int ncy, int nmr, const void* eta_e, 
   a.clov[1] = clover_slot(c, 1, 1);
   const size_t hb = spinor_bytes(1, c->g.vh);
   for (void** f : {&c->sap_res, &c->sap_delta})
-    if (!*f && hipMalloc(f, 2 * hb) != hipSuccess) {
-      *f = nullptr;
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "SAP workspace allocation failed");
-    }
+    if (!*f) LQ_TRY(device_alloc(f, 2 * hb, "SAP workspace allocation failed"));
   char* res = static_cast<char*>(c->sap_res);
   char* del = static_cast<char*>(c->sap_delta);
   a.psi[0] = psi_e;

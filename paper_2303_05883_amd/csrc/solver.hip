@@ -28,14 +28,7 @@
 
 namespace lq {
 
-static int alloc(void** p, size_t bytes) {
-  if (hipMalloc(p, bytes) != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
-    return set_error(LQCD_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
-  }
-  return LQCD_OK;
-}
+static int alloc(void** p, size_t bytes) { return device_alloc(p, bytes, "solver workspace allocation failed"); }
 
 int InnerVecs::init(lqcd_ctx* c, int p, int xp) {
   prec = p;

@@ -166,10 +166,9 @@ extern "C" int lqcd_autotune(lqcd_ctx* c, int prec, const char* path) {
   constexpr int NB = 3;
   void* buf[2 * NB] = {};
   for (int k = 0; k < 2 * NB; ++k) {
-    if (hipMalloc(&buf[k], bytes) != hipSuccess) {
+    if (const int s = device_alloc(&buf[k], bytes, "autotune scratch allocation failed"); s != LQCD_OK) {
       for (int j = 0; j < k; ++j) (void)hipFree(buf[j]);
-      (void)hipGetLastError();
-      return set_error(LQCD_ENOMEM, "autotune scratch allocation failed");
+      return s;
     }
     (void)hipMemsetAsync(buf[k], 0, bytes, c->stream);
   }
@@ -289,10 +288,10 @@ extern "C" int lqcd_bandwidth_probe(lqcd_ctx* c, int kind, size_t bytes, int rep
   const size_t n = bytes / 16;
   void* a = nullptr;
   void* b = nullptr;
-  if (hipMalloc(&a, n * 16) != hipSuccess || hipMalloc(&b, kind == 1 ? n * 16 : 256) != hipSuccess) {
-    if (a) (void)hipFree(a);
-    (void)hipGetLastError();
-    return set_error(LQCD_ENOMEM, "bandwidth probe allocation failed");
+  LQ_TRY(device_alloc(&a, n * 16, "bandwidth probe allocation failed"));
+  if (const int s = device_alloc(&b, kind == 1 ? n * 16 : 256, "bandwidth probe allocation failed"); s != LQCD_OK) {
+    (void)hipFree(a);
+    return s;
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
   int st = LQCD_OK;

@@ -136,8 +136,70 @@ static int no_heap_case() {
   return live.empty() ? 0 : 1;
 }
 
+// Where memory has run out, idle blocks of any context are given back, whichever call asks
+static int reclaim_case() {
+  std::vector<double> a(256 * 24 * 4), b(a);
+  lqcd_sap_params sap{};
+  sap.block[0] = 4, sap.block[1] = sap.block[2] = sap.block[3] = 4;
+  sap.ncycles = sap.nmr = 1;
+  const double* bs = a.data();
+  double* xs = b.data();
+  const int one = 1;
+  double gbs = 0;
+  lqcd_ctx* other = nullptr;
+  const int dims[4] = {4, 4, 4, 4};
+  for (int call = 0; call < 7; ++call)
+    for (int mine = 0; mine < 2; ++mine) {
+      lqcd_ctx *c = context(8, 8, 8, 8), *d = context(4, 4, 4, 4);
+      std::vector<double> f(4096 * 24), g(f);
+      bs = f.data(), xs = g.data();
+      OK(lqcd_stag_apply(mine ? c : d, LQCD_STAG_D, 0, 0.1, f.data(), g.data(), 0));
+      full = true;
+      switch (call) {
+        case 0: OK(lqcd_apply_native(c, LQCD_DPREC_SCHUR, 2, f.data(), g.data())); break;
+        case 1: OK(lqcd_solve(c, f.data(), g.data(), nullptr, nullptr)); break;
+        case 2: OK(lqcd_apply_sap(c, &sap, f.data(), g.data(), 0)); break;
+        case 3: OK(lqcd_solve_batch(&c, &one, &bs, &xs, 1, nullptr, nullptr)); break;
+        case 4: OK(lqcd_bandwidth_probe(c, 1, 1 << 20, 1, &gbs)); break;
+        case 5: OK(lqcd_create(dims, -1, nullptr, &other)); lqcd_destroy(other); break;
+        case 6: {
+          std::vector<double> h(4096 * 24 * 4), k(h);
+          OK(lqcd_dwf_apply_schur(c, &DWF, 0, 1, h.data(), k.data(), 0));
+        }
+      }
+      if (full) return std::printf("call %d asked for no memory\n", call), 1;
+      lqcd_destroy(c);
+      lqcd_destroy(d);
+      if (!live.empty()) return std::printf("call %d: blocks left\n", call), 1;
+    }
+  return 0;
+}
+
+// Idle blocks of all contexts together stay within 2 GiB, the ones idle longest go first,
+// and a context's go with it
+static int bound_case() {
+  double* dev = nullptr;
+  double* any = reinterpret_cast<double*>(&dev);
+  lqcd_dwf_params d = DWF;
+  lqcd_ctx* c[3] = {context(32, 32, 32, 32), context(32, 32, 32, 32), context(16, 32, 32, 32)};
+  const size_t base = live_bytes;
+  for (int k = 0; k < 12; ++k) {
+    d.Ls = 1 + k % 4;
+    OK(lqcd_dwf_apply(c[k % 3], &d, 0, k & 1, any, any + 1, 1));
+    if (live_bytes - base > (size_t)2 << 30) return std::printf("%zu bytes idle\n", live_bytes - base), 1;
+  }
+  if (live_bytes == base) return std::printf("nothing kept\n"), 1;
+  const long before = frees;
+  OK(lqcd_dwf_apply(c[2], &d, 0, 1, any, any + 1, 1));  // the last call again: its blocks are there
+  if (frees != before) return std::printf("a kept block was freed\n"), 1;
+  for (auto* x : c) lqcd_destroy(x);
+  return live.empty() ? 0 : 1;
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "no_heap") return no_heap_case();
+  if (name == "reclaim") return reclaim_case();
+  if (name == "bound") return bound_case();
   return 2;
 }
