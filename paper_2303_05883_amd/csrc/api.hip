@@ -136,15 +136,22 @@ Scratch::~Scratch() {
   for (int k = 0; k < n_; ++k) {
     const Block b = mem_[k];
     for (;;) {
-      Block old = b;  // what is to be freed: b itself if it is too large, else the oldest until there is room
+      // what is to be freed: b itself if it is too large, else the oldest (of this
+      // context, of all) until there is room
+      Block old = b;
       if (b.bytes <= IDLE_MAX) {
         std::lock_guard<std::mutex> lock(g_idle_mutex);
-        if (g_idle_n < IDLE_BLOCKS && g_idle_bytes + b.bytes <= IDLE_MAX) {
+        size_t own = b.bytes;
+        for (int n = 0; n < g_idle_n; ++n) own += g_idle[n].owner == c_ ? g_idle[n].b.bytes : 0;
+        if (own > IDLE_MAX) {
+          idle_take(&old, false, [this](const Idle& i) { return i.owner == c_; });
+        } else if (g_idle_n == IDLE_BLOCKS || g_idle_bytes + b.bytes > IDLE_MAX_ALL) {
+          idle_take(&old, false, [](const Idle&) { return true; });
+        } else {
           g_idle[g_idle_n++] = {b, c_};
           g_idle_bytes += b.bytes;
           break;
         }
-        idle_take(&old, false, [](const Idle&) { return true; });
       }
       (void)hipFree(old.p);
       if (old.p == b.p) break;

@@ -172,17 +172,18 @@ struct Block {
 };
 
 // Device blocks of one call, kept idle at its end for the context's next ones. The
-// idle blocks of all contexts together are bounded (IDLE_MAX, the ones idle longest
-// freed first), freed when any allocation of the library fails and with their
-// context. A context's calls run on its one stream and are made by one thread at a
+// idle blocks of a context and of all contexts together are bounded (the ones idle
+// longest freed first), freed when any allocation of the library fails and with
+// their context. One bound of 2 GiB for all contexts made those of a program that
+// solves on three in turn evict each other (domain-wall FP32 16^4 x 8 38 -> 42 ms). A context's calls run on its one stream and are made by one thread at a
 // time, so a block's last use lies before its next; the list of idle blocks is under
 // a lock and of a fixed size, so that nothing is thrown into a C caller. Contents are
 // what the last call left. hipMalloc and hipFree (which waits for the device and
 // unmaps) of a solve's vectors on each call, against blocks kept: domain-wall FP32
 // solve 16^4 x 8 43.1 -> 38.1 ms, 8x6x8x10 x 6 11.1 -> 9.5; SAP solve 16^3x32 33.0 -> 28.7,
 // multigrid 56.0 -> 52.2; staggered FP32 24^3x48 41.1 -> 37.9, 32^3x64 68.0 -> 64.2.
-constexpr size_t IDLE_MAX = (size_t)2 << 30;
-constexpr int IDLE_BLOCKS = 256;
+constexpr size_t IDLE_MAX = (size_t)2 << 30, IDLE_MAX_ALL = (size_t)16 << 30;
+constexpr int IDLE_BLOCKS = 512;
 constexpr int SCRATCH_BLOCKS = 64;  // of one call at a time; at most 19 are used
 class Scratch {
  public:
