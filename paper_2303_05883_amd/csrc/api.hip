@@ -665,10 +665,13 @@ static int validate_dwf(const lqcd_dwf_params* d) {
   return LQCD_OK;
 }
 
-// zeroed device buffers for the rest of the call
+// zeroed device buffers for the rest of the call, which ends with the stream
+// synchronised also where it fails: a copy from the caller's memory may be under way
 struct Bufs {
   Scratch mem;
-  explicit Bufs(lqcd_ctx* c) : mem(c) {}
+  hipStream_t stream;
+  explicit Bufs(lqcd_ctx* c) : mem(c), stream(c->stream) {}
+  ~Bufs() { (void)hipStreamSynchronize(stream); }
   int get(lqcd_ctx* c, size_t bytes, void** out) {
     LQ_TRY(mem.get(bytes, out, "device buffer allocation failed"));
     LQ_HIP(hipMemsetAsync(*out, 0, bytes, c->stream));

@@ -136,6 +136,31 @@ static int no_heap_case() {
   return live.empty() ? 0 : 1;
 }
 
+// A call that fails for want of memory has no copy from the caller's memory under way
+static int failed_copy_case() {
+  std::vector<double> a(256 * 24 * 4), b(a);
+  for (int call = 0; call < 6; ++call)
+    for (int n = 0, failed = 1; failed; ++n) {
+      lqcd_ctx* c = context(4, 4, 4, 4);
+      fail_at = n;
+      int s = LQCD_OK;
+      switch (call) {
+        case 0: s = lqcd_dwf_apply(c, &DWF, 0, 0, a.data(), b.data(), 0); break;
+        case 1: s = lqcd_dwf_apply_schur(c, &DWF, 0, 0, a.data(), b.data(), 0); break;
+        case 2: s = lqcd_dwf_solve(c, &DWF, a.data(), b.data(), nullptr, nullptr); break;
+        case 3: s = lqcd_dwf_solve_eo(c, &DWF, a.data(), b.data(), nullptr, nullptr); break;
+        case 4: s = lqcd_stag_apply(c, LQCD_STAG_D, 0, 0.1, a.data(), b.data(), 0); break;
+        case 5: s = lqcd_stag_solve(c, 0.1, a.data(), b.data(), nullptr, nullptr); break;
+      }
+      failed = fail_at < 0;  // the allocation of that number was asked for
+      fail_at = -1;
+      if (failed && s != LQCD_ENOMEM) return std::printf("call %d, allocation %d: status %d\n", call, n, s), 1;
+      if (copying) return std::printf("call %d, allocation %d: a copy is under way\n", call, n), 1;
+      lqcd_destroy(c);
+    }
+  return live.empty() ? 0 : 1;
+}
+
 // Where memory has run out, idle blocks of any context are given back, whichever call asks
 static int reclaim_case() {
   std::vector<double> a(256 * 24 * 4), b(a);
@@ -214,6 +239,7 @@ static int bound_case() {
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "no_heap") return no_heap_case();
+  if (name == "failed_copy") return failed_copy_case();
   if (name == "reclaim") return reclaim_case();
   if (name == "bound") return bound_case();
   return 2;

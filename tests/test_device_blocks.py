@@ -18,7 +18,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["no_heap", "reclaim", "bound"])
+@pytest.mark.parametrize("case", ["no_heap", "failed_copy", "reclaim", "bound"])
 def test_case(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
