@@ -754,8 +754,10 @@ int prolong_to(lqcd_ctx* c, MgState& s, const float2* e, void* x2) {
   return LQCD_OK;
 }
 
-// lanes per coarse row: 16 while that leaves at most 2 waves per SIMD on the
-// 256 CUs (2048 workgroups of 4 waves), else 4. Workgroups of a capply launch:
+// lanes per coarse row: 16 up to 2048 workgroups of 4 waves (8 waves per SIMD on the 256
+// CUs), else 4. Microseconds per coarse iteration with 16 and with 4 lanes: 512 rows
+// 17.7 and 27.6, 8192 23.5 and 29.8, 32768 (the border) 53.1 and 60.8, 49152 96.9 and
+// 100.9, 65536 63.0 and 59.7. Workgroups of a capply launch:
 int capply_sub(const MgState& s) { return s.nc() * 16 <= (size_t)2048 * 256 ? 16 : 4; }
 int capply_blocks(const MgState& s) { return grid1(s.nc() * capply_sub(s)); }
 
