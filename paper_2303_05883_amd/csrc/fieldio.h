@@ -380,22 +380,28 @@ __device__ inline void reconstruct(const cx<T> u[6], cx<T> r2[3]) {
 // the sum stays small until its last addition. Rounding error of A psi against long
 // double (8^4, c_SW 1, FP64 / FP32): 1.15e-16 / 6.0e-8; the diagonal first, products
 // rounded before they are added, 1.49e-16 / 7.8e-8; the diagonal first with serial
-// multiply-adds 1.87e-16 / 1.0e-7.
-template <typename T>
+// multiply-adds 1.87e-16 / 1.0e-7. That last form (DIAG_FIRST) stays in the hops of
+// several right-hand sides: the diagonal kept to the end takes their FP16 form from 128
+// to 134 VGPRs and from 4 to 3 waves per SIMD (36 right-hand sides 1077 -> 1231 us).
+template <bool DIAG_FIRST = false, typename T>
 __device__ inline void herm6_mul(const cx<T> m[18], const cx<T> x[6], cx<T> y[6]) {
   const T d[6] = {m[0].r, m[0].i, m[1].r, m[1].i, m[2].r, m[2].i};
+  if (DIAG_FIRST)
+#pragma unroll
+    for (int a = 0; a < 6; ++a) y[a] = d[a] * x[a];
   int k = 3;
 #pragma unroll
   for (int a = 0; a < 6; ++a) {
 #pragma unroll
     for (int b = a + 1; b < 6; ++b) {
       const cx<T> c = m[k++];
-      y[a] = a == 0 && b == 1 ? c * x[b] : cmadd(c, x[b], y[a]);
-      y[b] = a == 0 ? cmulc(c, x[a]) : cmaddc(c, x[a], y[b]);
+      y[a] = !DIAG_FIRST && a == 0 && b == 1 ? c * x[b] : cmadd(c, x[b], y[a]);
+      y[b] = !DIAG_FIRST && a == 0 ? cmulc(c, x[a]) : cmaddc(c, x[a], y[b]);
     }
   }
+  if (!DIAG_FIRST)
 #pragma unroll
-  for (int a = 0; a < 6; ++a) y[a] = caxpy(d[a], x[a], y[a]);
+    for (int a = 0; a < 6; ++a) y[a] = caxpy(d[a], x[a], y[a]);
 }
 
 // out = A psi with A given by its two chiral blocks (1/2 of the basis change folded in).

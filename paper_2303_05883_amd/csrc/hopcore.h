@@ -413,7 +413,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6];
-      herm6_mul(mb, acc[q], yv);
+      herm6_mul<true>(mb, acc[q], yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) acc[q][k] = yv[k];
     }
@@ -422,7 +422,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6], out[12];
-      herm6_mul(mb, acc[q] + 6, yv);
+      herm6_mul<true>(mb, acc[q] + 6, yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
         out[k] = acc[q][k] + yv[k];
@@ -454,7 +454,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6];
-      herm6_mul(mb, xo[q], yv);
+      herm6_mul<true>(mb, xo[q], yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) xo[q][k] = yv[k];
     }
@@ -463,7 +463,7 @@ __device__ inline void hop_site_multi(const HopArgs& a, const MultiPtrs<NB>& m, 
     for (int q = 0; q < NB; ++q) {
       if (!((m.act >> q) & 1u)) continue;
       cx<T> yv[6], out[12];
-      herm6_mul(mb, xo[q] + 6, yv);
+      herm6_mul<true>(mb, xo[q] + 6, yv);
 #pragma unroll
       for (int k = 0; k < 6; ++k) {
         out[k] = caxpy(sc, acc[q][k], xo[q][k] + yv[k]);
