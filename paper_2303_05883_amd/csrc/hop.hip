@@ -312,8 +312,9 @@ __global__ void __launch_bounds__(256) k_hop(HopArgs a) {
 // The full operator in one launch: 8 blocks (one per XCD) of the even sites, then
 // the 8 of the same ranges of the odd sites, out_p = A_pp x_p + scale H x_{1-p}.
 // Each link is a forward link of one parity and a backward link of the other and
-// each spinor the own site of one and a neighbour of the other, so both are read
-// from memory about once instead of twice, and a small lattice needs one launch.
+// each spinor the own site of one and a neighbour of the other, and a small lattice
+// needs one launch. At 32^3x64 in FP64 680 us, bound by what misses the L2s: 4.8 GB are
+// fetched (2.4 compulsory), about 7 TB/s with the Infinity Cache's share.
 // CANON: the result goes straight to the canonical field. lqcd_apply of D with its
 // conversions, against one launch per parity, its own export and an import per
 // parity: FP64 clover 8^4 67 -> 50 us, 24^3x48 435 -> 289, 32^3x64 1242 -> 829; FP32
